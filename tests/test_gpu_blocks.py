@@ -1,0 +1,53 @@
+"""Edges of the kernels' work splits on the GPU: the list of near traces and
+the trace blocks of migration, its kept source legs and trace parts, the bin
+search, the moveout's lag blocks and depth parts, the filter's rows and the
+stream kernels, each at the sizes where a split begins or ends, against the
+FP64 oracle or float64.
+
+Migration's tolerance is the parity bar of band-limited traces, 1e-5 relative
+L2; the filter's 1e-6 of sum |h| max |x| (65 float32 roundings at most); the dot
+product is a float64 sum of exact products, 1e-12 of the sum of magnitudes."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import trace_filter as oracle_filter
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ops():
+    from paper_1204_1225_amd import _lib, ops
+
+    _lib.load()
+    return ops
+
+
+# records of 40 900 samples leave room for the tight rows only
+@pytest.mark.parametrize("n,n_t,K,center,stride", [(1, 1, 1, 0, 1), (5, 7, 3, 1, 8), (4, 8, 65, 32, 8),
+                                                   (9, 1499, 66, 0, 1500), (3, 1503, 67, 66, 1503),
+                                                   (2, 5000, 64, 20, 5000), (2, 40900, 5, 2, 40900)])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_filter_splits(ops, n, n_t, K, center, stride, adjoint):
+    rng = np.random.default_rng(n_t + K)
+    x = rng.standard_normal((n, n_t)).astype(np.float32)
+    h = rng.standard_normal(K).astype(np.float32)
+    buf = torch.zeros((n, stride), device="cuda")
+    buf[:, :n_t] = torch.from_numpy(x).cuda()
+    t = buf[:, :n_t]
+    ref = (oracle_filter.adjoint if adjoint else oracle_filter.forward)(x, h, center)
+    tol = 1e-6 * float(np.abs(h).sum()) * float(np.abs(x).max())
+    got = ops.trace_filter(t, torch.from_numpy(h).cuda(), center, adjoint=adjoint)
+    assert np.abs(got.cpu().numpy() - ref).max() <= tol
+    ops.trace_filter(t, torch.from_numpy(h).cuda(), center, adjoint=adjoint, out=t)  # in place
+    assert torch.equal(t, got)
+
+
+def test_filter_infinity_stays_within_its_taps(ops):
+    x = torch.zeros((1, 200), device="cuda")
+    x[0, 100] = float("inf")
+    h = torch.ones(5, device="cuda")
+    y = ops.trace_filter(x, h, 2)[0].cpu().numpy()
+    assert np.isinf(y[98:103]).all() and (y[:98] == 0).all() and (y[103:] == 0).all()
