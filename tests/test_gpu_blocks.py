@@ -13,6 +13,8 @@ import pytest
 import torch
 
 from oracle import trace_filter as oracle_filter
+from paper_1204_1225_amd import survey
+from test_gpu_cig import check_moveout
 
 pytestmark = pytest.mark.gpu
 
@@ -23,6 +25,27 @@ def ops():
 
     _lib.load()
     return ops
+
+
+# bins, ny, nx, nz, lags, window
+@pytest.mark.parametrize("shape", [(3, 1, 3, 33, 0, None), (16, 1, 4, 100, 4, (7, 90)), (17, 2, 2, 63, 12, None),
+                                   (40, 1, 2, 64, 20, (0, 1)), (300, 1, 1, 24, 3, None), (2, 1, 2, 30, 40, None)])
+def test_moveout_splits(ops, shape):
+    nb, ny, nx, nz, lag, win = shape
+    rng = np.random.default_rng(nb + nz)
+    base = survey.bandlimited_noise(rng, ny * nx, nz + 8, 0.004)
+    img = np.stack([np.roll(base, b % 3, axis=1)[:, :nz] for b in range(nb)]).reshape(nb, ny, nx, nz)
+    img = (img + 0.2 * rng.standard_normal(img.shape)).astype(np.float32)
+    off = np.linspace(10.0, 900.0, nb).astype(np.float32)
+    z_lo, z_hi = win or (0, nz)
+    got = ops.cig_moveout(torch.from_numpy(img).cuda(), torch.from_numpy(off).cuda(), lag, z_lo, z_hi)
+    if lag == 0:  # one lag: no runner-up to compare with
+        S = img.astype(np.float64).sum(0)
+        C = (S * img.astype(np.float64))[..., z_lo:z_hi].sum(-1)
+        assert not torch.any(got[1])
+        assert np.abs(got[2].cpu().numpy() - C).max() <= 1e-6 * np.abs(C).max()
+        return
+    check_moveout(img, off, lag, z_lo, z_hi, got)
 
 
 # records of 40 900 samples leave room for the tight rows only
