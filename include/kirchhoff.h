@@ -355,7 +355,9 @@ km_status km_cig_moveout(const float* image, const km_grid* grid, const float* o
  * op: 0 = migrate, 1 = demigrate.  A tile is a compiled shape (waves, column
  * groups, depth slots, LDS budget; km_tile_count(op) of them) and a runtime
  * level of it, passed as tile = shape + 64 * level, level < km_tile_levels(op):
- * migrate levels 0..3 scale the trace block's LDS budget (traces per block) by
+ * a migrate shape may deal the traces out among several wavefronts on the same
+ * columns (column waves = waves / parts): its images differ from the other shapes' in
+ * rounding; migrate levels 0..3 scale the trace block's LDS budget (traces per block) by
  * 1, 0.5, 1.5 and 2 (at most 160 KiB); migrate levels 4 and 5 (lds16 = 1) take
  * budgets 1 and 2 and stage KM_BF16 / KM_F16 traces in LDS as their 16-bit
  * storage, widened and scaled as they are read (more traces per block, an
@@ -444,7 +446,7 @@ km_status km_batch_create(const km_problem* probs, int32_t n, int32_t op, int32_
  * in a static scratch array of 8 MiB per GPU (held from module load to process
  * end): at most 4096 problems and as many work items as fit in it
  * (about 460 000 at 16 bytes after the problem table; one work item per
- * (bin, column tile of waves x column groups x 4 columns, depth chunk of
+ * (bin, column tile of column waves x column groups x 4 columns, depth chunk of
  * 16 x depth slots)); larger batches return KM_E_UNSUPPORTED with the size
  * they need.  The call measures the item costs (synchronising the stream),
  * uploads the tables, resets the queue counter with a kernel and launches the

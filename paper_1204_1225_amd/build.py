@@ -21,6 +21,8 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libkirchhoff.so")
 SOURCES = ["km_api.cpp", "km_count.cpp", "km_migrate.hip", "km_demigrate.hip", "km_misc.hip", "km_cig.hip",
            "km_filter.hip"]
+# sources compiled once more per tile shape (-DKM_PART=i), so that the shapes compile in parallel
+PARTS = {"km_migrate.hip": 9}
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
@@ -28,9 +30,19 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
          "-Wall", "-Wno-unused-function", f"-I{INCLUDE}", f"-I{CSRC}"]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+def _units():
+    """(source, object, extra flags) of every compilation, the longest first."""
+    units = [(s, _object(s, k), [f"-DKM_PART={k}"]) for s, n in PARTS.items() for k in range(n)]
+    return units + [(s, _object(s), []) for s in SOURCES]
+
+
+def _object(src: str, part=None) -> str:
+    return os.path.join(BUILD, os.path.splitext(src)[0] + ("" if part is None else f"_{part}") + ".o")
+
+
+def _compile(unit) -> str:
+    src, obj, extra = unit
+    cmd = [HIPCC, *FLAGS, *extra, "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         msg = "\n".join(l for l in (r.stdout + r.stderr).splitlines() if "packed-fp32-ops" not in l)
@@ -41,9 +53,10 @@ def _compile(src: str) -> str:
 def build(verbose: bool = True) -> str:
     """Compile every HIP source and link libkirchhoff.so; returns its path."""
     os.makedirs(BUILD, exist_ok=True)
-    jobs = min(len(SOURCES), max(1, min(8, os.cpu_count() or 1)))
+    units = _units()
+    jobs = min(len(units), max(1, min(8, os.cpu_count() or 1)))
     with cf.ThreadPoolExecutor(jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, units))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -78,7 +91,7 @@ def build_sanitized(out: str) -> str:
     UndefinedBehaviorSanitizer checks; the device code is the normal one.  The
     sanitizer runtime is not linked in: load the library into a process that
     preloads asan_runtime()."""
-    objs = [os.path.join(BUILD, os.path.splitext(f)[0] + ".o") for f in SOURCES if f not in HOST_SOURCES]
+    objs = [obj for src, obj, _ in _units() if src not in HOST_SOURCES]
     if not all(os.path.exists(o) for o in objs):
         build(verbose=False)
     work = os.path.join(BUILD, "sanitize")

@@ -162,7 +162,7 @@ int traces_per_block(int lt, int budget, int ks, int row_bytes_per_sample) {
 // slots for the longest records.  Sets P.tb and P.cap (floats); false if a
 // record does not fit in LDS.
 constexpr int kMigrateSlots = 128;
-bool migrate_block_params(km::Params& P, int budget, int ks) {
+bool migrate_block_params(km::Params& P, int budget, int ks, int waves) {
     // square-root times stage (sample, difference) pairs, table times samples,
     // 16-bit staging packed pairs of 16-bit samples and 16-bit samples (half
     // as many bytes), anti-aliasing float64 running sums over nt + 4 max_half
@@ -170,18 +170,25 @@ bool migrate_block_params(km::Params& P, int budget, int ks) {
     const int64_t nt = P.nt;
     const int64_t need = (P.aa_max > 0 ? 2 * (nt + 4 * P.aa_max + 9)
                           : P.ttab   ? (P.s16 ? (nt + 4) / 2 : nt + 3)
-                                     : (P.s16 ? nt + 2 : 2 * (nt + 2))) + 3 & ~int64_t{3};
-    for (int tb = kMigrateSlots; tb >= 1; tb /= 2) {
-        const int64_t fixed = static_cast<int64_t>(km::migrate_lds_words(0, tb, ks));
-        const int64_t cap = std::max<int64_t>((budget / 4 - fixed) & ~int64_t{3}, need);
-        if ((fixed + cap) * 4 <= kMaxLds) {
-            P.tb = tb;
-            P.cap = static_cast<int>(cap);
-            return true;
+                                     : (P.s16 ? nt + 2 : 2 * ((nt + 5) & ~int64_t{3}))) + 3 & ~int64_t{3};
+    // the list of near traces holds two passes of its filter, less beside the longest records
+    for (const int list_cap : {2 * km::list_threads(waves), km::list_threads(waves), km::kListMin}) {
+        P.list_cap = list_cap;
+        for (int tb = kMigrateSlots; tb >= 1; tb /= 2) {
+            const int64_t fixed = static_cast<int64_t>(km::migrate_lds_words(0, tb, ks, P.list_cap));
+            const int64_t cap = std::max<int64_t>((budget / 4 - fixed) & ~int64_t{3}, need);
+            if ((fixed + cap) * 4 <= kMaxLds) {
+                P.tb = tb;
+                P.cap = static_cast<int>(cap);
+                return true;
+            }
         }
     }
     return false;
 }
+
+// Image columns of a migrate workgroup.
+int tile_columns(const km::TileShape& S) { return S.waves / S.trace_parts * S.column_groups * 4; }
 
 int shape_count(int op) { return op == 0 ? km::migrate_shape_count() : km::demigrate_shape_count(); }
 
@@ -223,7 +230,7 @@ km_status shape_params(int op, int tile, km::Params& P) {
                         "tile %d stages 16-bit traces: it needs KM_BF16 or KM_F16 traces, float32 time precision "
                         "and no anti-alias filter", tile);
         const int budget = static_cast<int>(std::min<double>(kMaxLds, S.lds_budget * kMigrateBudgetScale[level]));
-        if (!migrate_block_params(P, budget, S.depth_slots)) P.tb = 0;
+        if (!migrate_block_params(P, budget, S.depth_slots, S.waves)) P.tb = 0;
     } else {
         // float64 rows; the four groups of a wavefront take four traces, so
         // whole quads of traces keep every group busy
@@ -237,8 +244,11 @@ km_status shape_params(int op, int tile, km::Params& P) {
     if (P.tb < 1) return fail(KM_E_UNSUPPORTED, "record of %d samples does not fit in LDS", P.nt);
     const int zchunk = 16 * S.depth_slots;
     P.n_zchunks = (P.nz + zchunk - 1) / zchunk;
+    // migrate: equal chunks of whole slot pairs
+    const int pairs = (P.nz + 31) / 32;
+    P.zspan = P.n_zchunks > 0 ? 32 * ((pairs + P.n_zchunks - 1) / P.n_zchunks) : zchunk;
     if (P.n_zchunks > 65535) return fail(KM_E_UNSUPPORTED, "nz = %d needs more than 65535 depth chunks", P.nz);
-    const int cols = S.waves * S.column_groups * 4;
+    const int cols = tile_columns(S);
     const int ncol = P.nx * P.ny;
     P.n_coltiles = (ncol + cols - 1) / cols;
     return KM_OK;
@@ -369,20 +379,37 @@ void tune_save_locked() {
 // Traveltime kinds of the cache key.
 enum { KIND_DSR = 0, KIND_TABLE = 1, KIND_AA = 2, KIND_LTABLE = 3 };
 
-// Untuned choice: the shapes measured fastest on the 3D survey (migrate:
-// 8 waves x 4 column groups x 8 slots; demigrate: 8 waves x 4 slots x 1
-// trace quad, and 16 waves x 8 slots x 3 quads with table traveltimes, whose
-// table gathers favour more traces per workgroup).  With the anti-alias
-// filter: migrate 16 waves x 4 column groups x 8 slots (the largest trace
-// blocks), demigrate 8 waves x 4 slots x 1 quad.  With laterally varying
-// tables (16 reads per pair): migrate 4 waves x 3 column groups x 16 slots,
-// demigrate 8 waves x 8 slots x 3 quads.
-int default_tile(int op, int kind) {
-    if (op == 0) return kind == KIND_AA ? 1 : kind == KIND_LTABLE ? 3 : 2;
-    if (kind == KIND_AA) return 3;
-    if (kind == KIND_LTABLE) return 4;
-    return kind == KIND_TABLE ? 1 : 3;
+// Workgroups of a migrate shape on an image (n_bins images of nx ny columns and nz depths).
+int64_t migrate_workgroups(int shape, const km_grid& g) {
+    const km::TileShape& S = km::migrate_shape(shape);
+    const int64_t cols = static_cast<int64_t>(g.nx) * g.ny, c = tile_columns(S), z = 16 * S.depth_slots;
+    return (cols + c - 1) / c * ((g.nz + z - 1) / z) * g.n_bins;
 }
+
+// Untuned choice for migration, from the workgroups each shape gives (workgroups: a
+// function of the shape, summed over a batch's problems).  A large tile stages
+// and examines a trace once for many columns; a small image needs small tiles
+// to fill 256 CUs, and the smallest ones several wavefronts on the same columns
+// with the traces dealt out among them (trace_parts).  Each line is where the two
+// sides ran alike: 3000 workgroups of tile 5 ran 14.6 ms against 14.8 ms with
+// tile 6, 576 of them 1.97 against 1.64 ms; 512 of tile 6 ran 0.064 ms against
+// 0.074 ms with tile 7, 256 of them 0.61 against 0.29 ms; 256 of tile 7 ran 0.29
+// ms against 0.38 ms with tile 8, 128 of them 0.090 against 0.065 ms.
+// Tile 2 (128 columns) where the grid of tile 5 would pass 2^32 threads.
+template <typename Workgroups>
+int default_migrate_tile(int kind, Workgroups workgroups) {
+    if (workgroups(5) >= int64_t{1} << 22) return 2;
+    if (workgroups(5) >= 1024) return 5;  // 64 columns x 128 depths
+    const int64_t n = workgroups(6);      // 16 columns x 128 depths, also of shape 7
+    if (n >= 400) return 6;
+    return n >= 192 ? 7 : 8;              // 4 parts on 16 columns x 128 or 64 depths
+}
+
+// Untuned choice for the adjoint: 8 waves x 4 slots x 1 trace quad, and 16
+// waves x 8 slots x 3 quads with table traveltimes, whose table gathers favour
+// more traces per workgroup; 8 waves x 8 slots x 3 quads with laterally varying
+// tables (16 reads per pair).
+int default_demigrate_tile(int kind) { return kind == KIND_LTABLE ? 4 : kind == KIND_TABLE ? 1 : 3; }
 
 // Whether a tile can run problems of a class: a tile of op, and a 16-bit
 // staging level only for 16-bit traces with float32 time and no anti-alias
@@ -396,7 +423,9 @@ bool tile_applies(int op, int tile, int dtype, int kind, int prec) {
 
 // The caller's tile, else the tuned tile of this problem's class (if it still
 // applies: a cache file may come from another build), else the default.
-km_status pick_tile(int op, int tile, int dtype, int kind, int prec, int nz, int nt, int* out) {
+// default_tile: a function that gives the default.
+template <typename Default>
+km_status pick_tile(int op, int tile, int dtype, int kind, int prec, int nz, int nt, Default default_tile, int* out) {
     if (tile >= 0) {
         int shape = 0, level = 0;
         if (!decode_tile(op, tile, &shape, &level))
@@ -415,7 +444,7 @@ km_status pick_tile(int op, int tile, int dtype, int kind, int prec, int nz, int
             return KM_OK;
         }
     }
-    *out = default_tile(op, kind);
+    *out = default_tile();
     return KM_OK;
 }
 
@@ -495,8 +524,10 @@ km_status migrate_impl(const km_traces* traces, const km_grid* grid, const km_tr
     if (grid_empty(grid)) return KM_OK;
     if (!image || !aligned(image, 4)) return fail(KM_E_INVALID, "kirchhoff_migrate: image is NULL or misaligned");
     int shape = 0;
-    st = pick_tile(0, tile, traces->dtype, lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR,
-                   tt->time_precision, grid->nz, traces->n_samples, &shape);
+    const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
+    st = pick_tile(0, tile, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples,
+                   [&] { return default_migrate_tile(kind, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
+                   &shape);
     if (st != KM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (traces->n_traces == 0 && !accumulate)
@@ -523,8 +554,9 @@ km_status demigrate_impl(const float* image, const km_grid* grid, const km_trave
     }
     if (!image || !aligned(image, 4)) return fail(KM_E_INVALID, "kirchhoff_demigrate: image is NULL or misaligned");
     int shape = 0;
-    st = pick_tile(1, tile, out->dtype, lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR,
-                   tt->time_precision, grid->nz, out->n_samples, &shape);
+    const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
+    st = pick_tile(1, tile, out->dtype, kind, tt->time_precision, grid->nz, out->n_samples,
+                   [&] { return default_demigrate_tile(kind); }, &shape);
     if (st != KM_OK) return st;
     return run_op(1, out, grid, tt, weight, const_cast<float*>(image), accumulate, shape, s, tab, aa, lat);
 }
@@ -956,7 +988,10 @@ struct BatchPlan {
     int64_t n_slots = 0;      // items over all problems
 };
 
-km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, const char* who, BatchPlan& B) {
+// max_items: work items the caller has room for; the untuned choice takes the
+// largest tile where its own tile makes more.
+km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t max_items, const char* who,
+                     BatchPlan& B) {
     if (!probs || n < 1) return fail(KM_E_INVALID, "%s: need n >= 1 problems", who);
     for (int i = 0; i < n; ++i) {
         km_status st = check_traces(&probs[i].traces, true, who);
@@ -977,7 +1012,16 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, const cha
         max_nz = std::max(max_nz, probs[i].grid.nz);
         max_nt = std::max(max_nt, probs[i].traces.n_samples);
     }
+    const auto workgroups = [&](int sh) {
+        int64_t w = 0;
+        for (int i = 0; i < n; ++i) w += migrate_workgroups(sh, probs[i].grid);
+        return w;
+    };
     km_status st = pick_tile(0, tile, probs[0].traces.dtype, KIND_DSR, probs[0].tt.time_precision, max_nz, max_nt,
+                             [&] {
+                                 const int t = default_migrate_tile(KIND_DSR, workgroups);
+                                 return workgroups(t) > max_items ? 2 : t;
+                             },
                              &B.tile);
     if (st != KM_OK) return st;
     B.shape = B.tile % kTileLevelStride;
@@ -1026,7 +1070,7 @@ km_status batch_items(BatchPlan& B, unsigned long long* d_costs, hipStream_t s, 
     for (size_t i = 0; i < B.P.size(); ++i) {
         const km::Params& P = B.P[i];
         const int64_t nslot = static_cast<int64_t>(P.n_bins) * P.n_zchunks * P.n_coltiles;
-        hipError_t e = km::launch_item_costs(P, S.depth_slots, S.waves * S.column_groups * 4, d_costs, s);
+        hipError_t e = km::launch_item_costs(P, tile_columns(S), d_costs, s);
         if (e == hipSuccess && nslot > 0)
             e = hipMemcpyAsync(h.data(), d_costs, sizeof(unsigned long long) * nslot, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1129,7 +1173,7 @@ km_status km_batch_create(const km_problem* probs, int32_t n, int32_t op, int32_
     km_batch* B = new (std::nothrow) km_batch();
     if (!B) return fail(KM_E_NOMEM, "km_batch_create: host allocation failed");
     hipGetDevice(&B->device);
-    km_status st = batch_plan(probs, n, tile, "km_batch_create", B->plan);
+    km_status st = batch_plan(probs, n, tile, int64_t{1} << 31, "km_batch_create", B->plan);
     if (st != KM_OK) {
         batch_free(B);
         return st;
@@ -1196,7 +1240,7 @@ km_status km_batch_migrate_static(const km_problem* probs, int32_t n, int32_t ti
     const char* who = "km_batch_migrate_static";
     hipStream_t s = static_cast<hipStream_t>(stream);
     BatchPlan L;
-    km_status st = batch_plan(probs, n, tile, who, L);
+    km_status st = batch_plan(probs, n, tile, (kScratchBytes - kScratchItemsOffset) / sizeof(int4), who, L);
     if (st != KM_OK) return st;
     if (static_cast<size_t>(n) > kScratchProblems)
         return fail(KM_E_UNSUPPORTED, "%s: %d problems exceed the static scratch's %zu", who, n, kScratchProblems);

@@ -46,14 +46,6 @@ __device__ __forceinline__ void index_range(const float* __restrict__ v, int n, 
     }
 }
 
-// Bits of the four 16-lane groups of a ballot, OR-ed / AND-ed into 16 bits.
-__device__ __forceinline__ uint32_t fold_or(uint64_t m) {
-    return static_cast<uint32_t>((m | (m >> 16) | (m >> 32) | (m >> 48)) & 0xFFFFull);
-}
-__device__ __forceinline__ uint32_t fold_and(uint64_t m) {
-    return static_cast<uint32_t>((m & (m >> 16) & (m >> 32) & (m >> 48)) & 0xFFFFull);
-}
-
 // Two slots with a per-lane aperture mask, their taps merged by address.  The
 // two slots of a pair are adjacent depths of one lane, so their samples i0 and
 // i1 are usually equal or neighbours: the second slot's taps that land on i0
@@ -469,9 +461,9 @@ __device__ __forceinline__ void demigrate_segment(const Params& P, int b, int t0
     by = wave_max(by);
 
     for (int zc = 0; zc < P.n_zchunks; ++zc) {
-        const int z0 = chunk_z0<true>(P.nz, zc, P.n_zchunks, KS * kGroup);
+        const int z0 = chunk_z0_bottom(P.nz, zc, P.n_zchunks, KS * kGroup);
         ChunkTables<KS> T;
-        load_chunk_tables<KS, kIL, TT, PX>(P, z0, d, WK == W_COSCOS, T, nullptr);
+        load_chunk_tables<KS, kIL, TT, PX>(P, z0, P.nz, d, WK == W_COSCOS, T, nullptr);
         if (!(T.rmax >= 0.0f)) continue;
         float S[KS];
 #pragma unroll
@@ -506,7 +498,7 @@ template <int NW, int KS, int NQ, bool TF, int WK, int TT = TT_DSR, bool PX = fa
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(KS <= 4 && TT == TT_DSR ? 6 : 1)))
 void demigrate_kernel(Params P) {
     static_assert(!(PX && TT == TT_AA), "no extended-precision anti-alias kernels");
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     double* sAcc = reinterpret_cast<double*>(lds);                     // [tb][lt]
     float4* sGeo = reinterpret_cast<float4*>(lds + 2 * P.tb * P.lt);   // [tb]
     float* sInvSq = lds + 2 * P.tb * P.lt + 4 * P.tb;                  // [kAAMaxHalf + 2]: 1 / n^2
@@ -638,7 +630,7 @@ static hipError_t launch_demigrate_shape(const Params& P, hipStream_t s) {
     X(8, 8, 3, 147456)
 
 static const TileShape kDemigrateShapes[] = {
-#define X(nw, ks, nq, lb) {nw, 1, ks, lb, nq},
+#define X(nw, ks, nq, lb) {nw, 1, ks, lb, nq, 1},
     KM_DEMIGRATE_SHAPES(X)
 #undef X
 };

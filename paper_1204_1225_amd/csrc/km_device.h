@@ -60,7 +60,9 @@ struct Params {
     int32_t lt;       // demigrate: LDS row length (multiple of 4, >= nt + kLead + 2)
     int32_t tb;       // traces per LDS block (migrate: at most)
     int32_t cap;      // migrate: LDS floats for the staged time windows of a block
+    int32_t list_cap; // migrate: entries of the list of near traces
     int32_t n_zchunks;
+    int32_t zspan;    // migrate: depths per chunk
     int32_t n_coltiles;
     // table traveltimes (used by the TABLE kernels instead of t0sq / s2)
     const float* ttab;  // [n_h][nz] one-way seconds at h = ih * dh
@@ -115,6 +117,32 @@ __device__ __forceinline__ int64_t lower_bound_bin(const int32_t* __restrict__ b
         if (bin[mid] < key) lo = mid + 1; else hi = mid;
     }
     return lo;
+}
+
+// Range [lo, hi) of the entries of sorted bin[0..n) equal to b.  One wavefront:
+// 64 probes per step for each end (3 steps for 200 000 traces, where a binary
+// search waits for 18 loads one after the other, twice).
+__device__ __forceinline__ void bin_range(const int32_t* __restrict__ bin, int64_t n, int32_t b, int64_t& lo,
+                                          int64_t& hi) {
+    const int lane = threadIdx.x & (kLanes - 1);
+    // lo (hi) = number of entries < b (<= b): within [l, l + m) ([h, h + m)) of the candidates
+    int64_t l = 0, h = 0, ml = n, mh = n;
+    while (ml > 0 || mh > 0) {
+        const int64_t sl = (ml + kLanes - 1) / kLanes, sh = (mh + kLanes - 1) / kLanes;
+        const int64_t il = sl * (lane + 1) - 1, ih = sh * (lane + 1) - 1;  // last entry of the lane's part
+        const bool ol = il >= 0 && il < ml, oh = ih >= 0 && ih < mh;
+        const int32_t vl = ol ? bin[l + il] : 0, vh = oh ? bin[h + ih] : 0;
+        const int cl = __builtin_popcountll(__builtin_amdgcn_ballot_w64(ol && vl < b));
+        const int ch = __builtin_popcountll(__builtin_amdgcn_ballot_w64(oh && vh <= b));
+        // cl whole parts lie below; the next one (without its last entry, if it has been seen) remains
+        const int64_t rl = ml - sl * cl, rh = mh - sh * ch;
+        l += sl * cl;
+        h += sh * ch;
+        ml = rl < sl ? rl : max<int64_t>(sl - 1, 0);
+        mh = rh < sh ? rh : max<int64_t>(sh - 1, 0);
+    }
+    lo = l;
+    hi = h;
 }
 
 __device__ __forceinline__ float widen16(uint32_t bits, int dtype) {
@@ -221,6 +249,25 @@ __device__ __forceinline__ PairX eval_pair_ext(float A, float B, double Hs, doub
     return p;
 }
 
+// One leg of eval_pair_ext: its time in seconds and its seed (migrate keeps a
+// source leg for the traces that share it; the pair's time is the legs' sum
+// over dt, which differs from eval_pair_ext's only in the last float64 bits).
+struct LegTimeX {
+    double t;
+    float q;
+};
+
+__device__ __forceinline__ LegTimeX leg_time_ext(float A, float B, double H) {
+    const double a = fma(static_cast<double>(B), H, static_cast<double>(A));
+    LegTimeX l;
+    l.q = __builtin_amdgcn_rsqf(static_cast<float>(a));
+    const double q = static_cast<double>(l.q);
+    const double y = a * q;
+    const double e = fma(-y, y, a);
+    l.t = fma(e * q, 0.5, y);
+    return l;
+}
+
 // Squared leg lengths in float64 from the float32 coordinates (the
 // differences and squares are exact; one rounding in the sum).
 struct LegsX {
@@ -250,17 +297,16 @@ struct PairAA {
     float f, r, alpha, beta;
 };
 
+// pair_aa takes the source leg's square root ss and its reciprocal is.
 template <bool TF, int WK>
-__device__ __forceinline__ PairAA eval_pair_aa(float A, float B, float hs2, float hr2, float tf_off, float wlo,
-                                               float whi, float dxs, float dys, float dxr, float dyr, float adx,
-                                               float ady, float lmax, const float* invsq) {
-    const float as = fmaf(B, hs2, A);
-    const float ar = fmaf(B, hr2, A);
-    const float ss = __builtin_amdgcn_sqrtf(as), sr = __builtin_amdgcn_sqrtf(ar);
+__device__ __forceinline__ PairAA pair_aa(float A, float B, float ss, float is, float hr2, float tf_off, float wlo,
+                                          float whi, float dxs, float dys, float dxr, float dyr, float adx, float ady,
+                                          float lmax, const float* invsq) {
+    const float sr = __builtin_amdgcn_sqrtf(fmaf(B, hr2, A));
     float w = ss + sr;
     if (TF) w = w + tf_off;
     w = __builtin_amdgcn_fmed3f(w, wlo, whi);
-    const float is = __builtin_amdgcn_rcpf(ss), ir = __builtin_amdgcn_rcpf(sr);
+    const float ir = __builtin_amdgcn_rcpf(sr);
     PairAA p;
     p.i = static_cast<int32_t>(w);
     p.f = __builtin_amdgcn_fractf(w);
@@ -276,6 +322,15 @@ __device__ __forceinline__ PairAA eval_pair_aa(float A, float B, float hs2, floa
     p.alpha = (1.0f - phi) * invsq[p.L];
     p.beta = phi * invsq[p.L + 1];
     return p;
+}
+
+template <bool TF, int WK>
+__device__ __forceinline__ PairAA eval_pair_aa(float A, float B, float hs2, float hr2, float tf_off, float wlo,
+                                               float whi, float dxs, float dys, float dxr, float dyr, float adx,
+                                               float ady, float lmax, const float* invsq) {
+    const float ss = __builtin_amdgcn_sqrtf(fmaf(B, hs2, A));
+    return pair_aa<TF, WK>(A, B, ss, __builtin_amdgcn_rcpf(ss), hr2, tf_off, wlo, whi, dxs, dys, dxr, dyr, adx, ady,
+                           lmax, invsq);
 }
 
 // Table traveltimes.  A leg's place in the table: the time at horizontal
@@ -328,10 +383,13 @@ __device__ __forceinline__ float table_read(const Params& P, int vbyte, int sbyt
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(raw_buffer(P.ttab, P.ttab_bytes), vbyte, sbyte, 0));
 }
 
-__device__ __forceinline__ double table_time_ext(const Params& P, TLegX L, int iz) {
-    const int vo = (L.off + iz) * 4;
+__device__ __forceinline__ double table_time_ext_at(const Params& P, double f, int vo) {
     const double a = table_read(P, vo, 0), b = table_read(P, vo, 4 * P.nz);
-    return fma(L.f, b - a, a);
+    return fma(f, b - a, a);
+}
+
+__device__ __forceinline__ double table_time_ext(const Params& P, TLegX L, int iz) {
+    return table_time_ext_at(P, L.f, (L.off + iz) * 4);
 }
 
 // Interpolated one-way time as a float32 table value (exact) plus a small
@@ -346,10 +404,14 @@ struct TTime {
     float base, inc;
 };
 
-__device__ __forceinline__ TTime table_time(const Params& P, TLeg L, int iz) {
-    const int vo = (L.off + iz) * 4;
+// vo: byte offset of the value in the table (the row at or before the leg).
+__device__ __forceinline__ TTime table_time_at(const Params& P, float f, int vo) {
     const float a = table_read(P, vo, 0), b = table_read(P, vo, 4 * P.nz);
-    return TTime{a, L.f * (b - a)};
+    return TTime{a, f * (b - a)};
+}
+
+__device__ __forceinline__ TTime table_time(const Params& P, TLeg L, int iz) {
+    return table_time_at(P, L.f, (L.off + iz) * 4);
 }
 
 // The pair's total time in samples: (T_s + T_r) / dt, the bases summed exactly.
@@ -411,21 +473,22 @@ __device__ __forceinline__ TTime ltable_lerp(float fh, LCol C, float a00, float 
     return TTime{a00, fmaf(C.fy, t1 - t0, t0)};
 }
 
-__device__ __forceinline__ TTime ltable_time(const Params& P, TLeg L, LCol C, int iz) {
-    const int vo = (C.off + L.off + iz) * 4;
+__device__ __forceinline__ TTime ltable_time_at(const Params& P, float f, LCol C, int vo) {
     const int nz = 4 * P.nz, dx = 4 * P.ldx, dy = 4 * P.ldy;  // byte offsets (scalar)
     const float a00 = table_read(P, vo, 0), b00 = table_read(P, vo, nz);
     const float a10 = table_read(P, vo, dx), b10 = table_read(P, vo, dx + nz);
     const float a01 = table_read(P, vo, dy), b01 = table_read(P, vo, dy + nz);
     const float a11 = table_read(P, vo, dx + dy), b11 = table_read(P, vo, dx + dy + nz);
-    return ltable_lerp(L.f, C, a00, b00, a10, b10, a01, b01, a11, b11);
+    return ltable_lerp(f, C, a00, b00, a10, b10, a01, b01, a11, b11);
+}
+
+__device__ __forceinline__ TTime ltable_time(const Params& P, TLeg L, LCol C, int iz) {
+    return ltable_time_at(P, L.f, C, (C.off + L.off + iz) * 4);
 }
 
 // ltable_time with an extended leg (the h fraction and the differences in float64).
-__device__ __forceinline__ double ltable_time_ext(const Params& P, TLegX L, LCol C, int iz) {
-    const int vo = (C.off + L.off + iz) * 4;
+__device__ __forceinline__ double ltable_time_ext_at(const Params& P, double fh, LCol C, int vo) {
     const int nz = 4 * P.nz, dx = 4 * P.ldx, dy = 4 * P.ldy;  // byte offsets (scalar)
-    const double fh = L.f;
     const double a00 = table_read(P, vo, 0), b00 = table_read(P, vo, nz);
     const double a10 = table_read(P, vo, dx), b10 = table_read(P, vo, dx + nz);
     const double a01 = table_read(P, vo, dy), b01 = table_read(P, vo, dy + nz);
@@ -437,6 +500,10 @@ __device__ __forceinline__ double ltable_time_ext(const Params& P, TLegX L, LCol
     return fma(fy, t1 - t0, t0);
 }
 
+__device__ __forceinline__ double ltable_time_ext(const Params& P, TLegX L, LCol C, int iz) {
+    return ltable_time_ext_at(P, L.f, C, (C.off + L.off + iz) * 4);
+}
+
 // Amplitude of a leg (the table kinds with P.tamp): the amplitude tables
 // interpolated as the times are, in float32 (a weight needs no more).
 __device__ __forceinline__ float amp_read(const Params& P, int vbyte, int sbyte) {
@@ -444,14 +511,12 @@ __device__ __forceinline__ float amp_read(const Params& P, int vbyte, int sbyte)
 }
 
 template <bool LAT>
-__device__ __forceinline__ float table_amp(const Params& P, int off, float fh, LCol C, int iz) {
+__device__ __forceinline__ float table_amp_at(const Params& P, float fh, LCol C, int vo) {
     const int nz = 4 * P.nz;
     if (!LAT) {
-        const int vo = (off + iz) * 4;
         const float a = amp_read(P, vo, 0), b = amp_read(P, vo, nz);
         return fmaf(fh, b - a, a);
     }
-    const int vo = (C.off + off + iz) * 4;
     const int dx = 4 * P.ldx, dy = 4 * P.ldy;
     const float a00 = amp_read(P, vo, 0), b00 = amp_read(P, vo, nz);
     const float a10 = amp_read(P, vo, dx), b10 = amp_read(P, vo, dx + nz);
@@ -461,6 +526,11 @@ __device__ __forceinline__ float table_amp(const Params& P, int off, float fh, L
     const float t01 = fmaf(fh, b01 - a01, a01), t11 = fmaf(fh, b11 - a11, a11);
     const float t0 = fmaf(C.fx, t10 - t00, t00), t1 = fmaf(C.fx, t11 - t01, t01);
     return fmaf(C.fy, t1 - t0, t0);
+}
+
+template <bool LAT>
+__device__ __forceinline__ float table_amp(const Params& P, int off, float fh, LCol C, int iz) {
+    return table_amp_at<LAT>(P, fh, C, ((LAT ? C.off : 0) + off + iz) * 4);
 }
 
 // Two adjacent depths iz, iz + 1 of one leg (the adjoint's interleaved slot
@@ -608,18 +678,88 @@ __device__ __forceinline__ void clamp_bounds(int lt, float& wlo, float& whi) {
     whi = TF ? static_cast<float>(lt - 2) : static_cast<float>(lt - 2 - kLead);
 }
 
-// First depth of depth chunk zc of n_chunks chunks of `span` depths.
-// BOTTOM = false: chunks start at depth 0 (a partial chunk holds the deepest
-// depths; its lanes past nz are invalid).  BOTTOM = true: chunks end at the
-// last depth, so a partial chunk holds the shallowest depths, where the
-// aperture is smallest and few pairs fall (its depths below 0 are invalid
-// lanes).  The adjoint takes the bottom alignment (5 % faster on the 3D survey:
-// its partial chunk no longer wastes half its lanes where the pairs are
-// densest); migration and the counting kernel keep the top one (migration ran
-// 28 % slower bottom-aligned).
-template <bool BOTTOM>
-__device__ __forceinline__ int chunk_z0(int nz, int zc, int n_chunks, int span) {
-    return BOTTOM ? zc * span - (n_chunks * span - nz) : zc * span;
+// A value that is equal in every lane, as a scalar register.
+__device__ __forceinline__ float uniform_f(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+// v, recomputed here: what depends on it is not moved out of the enclosing
+// loop (where it would hold registers through the loop's other phases).
+__device__ __forceinline__ int fresh_v(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Cross-lane steps without the LDS crossbar (a crossbar read costs an address
+// register that lives through the kernel's loops, and LDS latency).
+// dpp<CTRL>(v): v of another lane of the same 16-lane row: 0x110 + n takes lane
+// d - n (0 below the row's start), 0x120 + n rotates the row by n.
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+    return __int_as_float(dpp_i<CTRL>(__float_as_int(v)));
+}
+
+// Minimum / maximum over the lane's 16-lane group (every lane gets it).
+__device__ __forceinline__ float group_min(float v) {
+    v = fminf(v, dpp_f<0x128>(v));
+    v = fminf(v, dpp_f<0x124>(v));
+    v = fminf(v, dpp_f<0x122>(v));
+    return fminf(v, dpp_f<0x121>(v));
+}
+__device__ __forceinline__ float group_max(float v) {
+    v = fmaxf(v, dpp_f<0x128>(v));
+    v = fmaxf(v, dpp_f<0x124>(v));
+    v = fmaxf(v, dpp_f<0x122>(v));
+    return fmaxf(v, dpp_f<0x121>(v));
+}
+
+// Minimum / maximum over lanes d, 16 + d, 32 + d, 48 + d (every lane gets it):
+// the row swaps leave (rows 0, 0, 2, 2) and (1, 1, 3, 3), the half swaps
+// (rows 0, 1, 0, 1) and (2, 3, 2, 3).
+__device__ __forceinline__ float rows_min(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = fminf(__int_as_float(r[0]), __int_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+    return fminf(__int_as_float(r[0]), __int_as_float(r[1]));
+}
+__device__ __forceinline__ float rows_max(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    v = fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+    return fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
+}
+
+// Inclusive prefix sum over the wavefront: within the rows, then the row ends
+// are handed on (0x142: lane 15 of a row to the next row, 0x143: lane 31 to the
+// upper half).
+__device__ __forceinline__ int wave_scan(int v) {
+    v += dpp_i<0x111>(v);
+    v += dpp_i<0x112>(v);
+    v += dpp_i<0x114>(v);
+    v += dpp_i<0x118>(v);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+}
+
+// Wavefront minimum / maximum (every lane gets it, as a uniform value).
+__device__ __forceinline__ float wave_min(float v) { return uniform_f(rows_min(group_min(v))); }
+__device__ __forceinline__ float wave_max(float v) { return uniform_f(rows_max(group_max(v))); }
+
+// Depth chunks of migration and the counting kernel start at depth 0 and hold
+// Params::zspan depths (a multiple of 32, at most the shape's slots), so that
+// the last chunk is not left with a few depths; its lanes past the chunk's end
+// are invalid.  The adjoint's chunks hold the whole of their slots and end at
+// the last depth, so that a partial chunk holds the shallowest depths, where
+// the aperture is smallest and few pairs fall (its depths below 0 are invalid
+// lanes; 5 % faster on the 3D survey than chunks from depth 0: the partial
+// chunk no longer wastes half its lanes where the pairs are densest).
+// First depth of the adjoint's chunk zc of n_chunks chunks of `span` depths.
+__device__ __forceinline__ int chunk_z0_bottom(int nz, int zc, int n_chunks, int span) {
+    return zc * span - (n_chunks * span - nz);
 }
 
 // Depth of lane d in slot k of the chunk starting at z0.  IL = 1: slot k is
@@ -633,7 +773,8 @@ __device__ __forceinline__ int slot_depth(int z0, int k, int d) {
 }
 
 // Per-depth tables of one depth chunk.  Lane d of every group holds depth
-// slot_depth(z0, k, d) in slot k.  A lane is valid if its depth exists and (for
+// slot_depth(z0, k, d) in slot k.  A lane is valid if its depth exists in the
+// chunk (0 <= iz < z1) and (for
 // the cos*cos weight) t0sq > 0; elsewhere W = 0 and the image value is 0.
 //   A, B     sample-unit traveltime tables per slot
 //   R        the aperture table per slot (-1 where the lane is invalid)
@@ -653,7 +794,7 @@ struct ChunkTables {
 };
 
 template <int KS, int IL = 1, int TT = TT_DSR, bool PX = false>
-__device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int d, bool zero_weight_guard,
+__device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int z1, int d, bool zero_weight_guard,
                                                   ChunkTables<KS>& T, float* sR) {
     const int lane = threadIdx.x & (kLanes - 1);
     float rmax = -1.0f;
@@ -665,7 +806,7 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int d
         // invalid lanes: a = 1 for every leg (finite time and weight), never inside
         float A = 1.0f, B = 0.0f, R = -1.0f;
         bool valid = false;
-        if (iz >= 0 && iz < P.nz) {
+        if (iz >= 0 && iz < z1) {
             if (is_table(TT)) {
                 // table times carry no t0sq / s2; A, B are unused and W = 1
                 valid = true;
@@ -694,11 +835,8 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int d
         // min / max over the 16 lanes of the group (all groups hold the same depths)
         float lo = valid ? R : __builtin_inff();
         float hi = valid ? R : -__builtin_inff();
-#pragma unroll
-        for (int off = 1; off < kGroup; off <<= 1) {
-            lo = fminf(lo, __shfl_xor(lo, off, kLanes));
-            hi = fmaxf(hi, __shfl_xor(hi, off, kLanes));
-        }
+        lo = group_min(lo);
+        hi = group_max(hi);
         if (d == k) {
             rlo_mine = lo;
             rhi_mine = hi;
@@ -712,15 +850,24 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int d
     T.rmax = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(rmax)));
 }
 
-// Bit k (k < KS) set when slot k may hold a lane inside the aperture
-// (hmin <= max R of the slot) / when every valid lane is inside
-// (hmax <= min R of the slot).  hmin, hmax: wavefront-uniform.
+// Bits of the four 16-lane groups of a ballot, OR-ed / AND-ed into 16 bits.
+__device__ __forceinline__ uint32_t fold_or(uint64_t m) {
+    const uint32_t h = static_cast<uint32_t>(m) | static_cast<uint32_t>(m >> 32);
+    return (h | (h >> 16)) & 0xFFFFu;
+}
+__device__ __forceinline__ uint32_t fold_and(uint64_t m) {
+    const uint32_t h = static_cast<uint32_t>(m) & static_cast<uint32_t>(m >> 32);
+    return h & (h >> 16);
+}
+
+// Bit k (k < KS) set when slot k may hold a lane inside the aperture of some
+// group's column (hm <= max R of the slot) / when every valid lane is inside
+// for every group (hm <= min R of the slot; bits from 16 on are meaningless).
 template <int KS>
-__device__ __forceinline__ void slot_masks(const ChunkTables<KS>& T, float hmin, float hmax, uint64_t& any,
-                                           uint64_t& full) {
-    constexpr uint64_t kMask = (KS >= 64) ? ~0ull : ((1ull << KS) - 1ull);
-    any = __builtin_amdgcn_ballot_w64(hmin <= T.rhi) & kMask;
-    full = __builtin_amdgcn_ballot_w64(hmax <= T.rlo) & kMask;
+__device__ __forceinline__ void slot_masks(const ChunkTables<KS>& T, float hm, uint32_t& any, uint32_t& full) {
+    constexpr uint32_t kMask = (1u << KS) - 1u;
+    any = fold_or(__builtin_amdgcn_ballot_w64(hm <= T.rhi)) & kMask;
+    full = fold_and(__builtin_amdgcn_ballot_w64(hm <= T.rlo));
 }
 
 // Final per-depth factor of the image: t0sq / dt^4 for the cos*cos weight
@@ -732,24 +879,6 @@ __device__ __forceinline__ float depth_factor(const Params& P, int iz) {
     const float t0 = P.t0sq[iz];
     if (PX) return t0 > 0.0f ? t0 : 0.0f;
     return t0 > 0.0f ? static_cast<float>(static_cast<double>(t0) * P.wscale) : 0.0f;
-}
-
-// A value that is equal in every lane, as a scalar register.
-__device__ __forceinline__ float uniform_f(float v) {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-
-// Wavefront minimum / maximum (every lane gets it, as a uniform value).
-__device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-    for (int off = 1; off < kLanes; off <<= 1) v = fminf(v, __shfl_xor(v, off, kLanes));
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = 1; off < kLanes; off <<= 1) v = fmaxf(v, __shfl_xor(v, off, kLanes));
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 // Squared distance from (x, y) to the box [x0, x1] x [y0, y1] (0 inside), and
@@ -767,16 +896,13 @@ __device__ __forceinline__ float box_far2(float x, float y, float x0, float x1, 
     return dx * dx + dy * dy;
 }
 
-// v from lane `src` (any lane), through the LDS crossbar.
-__device__ __forceinline__ float lane_read(float v, int src) {
-    return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
+// v of the lane at crossbar byte address a (4 times the lane).
+__device__ __forceinline__ float bperm_f(int a, float v) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(a, __float_as_int(v)));
 }
-
-// A float64 value from lane `src` (two crossbar reads).
-__device__ __forceinline__ double lane_read_d(double v, int src) {
-    const int lo = __builtin_amdgcn_ds_bpermute(src << 2, __double2loint(v));
-    const int hi = __builtin_amdgcn_ds_bpermute(src << 2, __double2hiint(v));
-    return __hiloint2double(hi, lo);
+__device__ __forceinline__ double bperm_d(int a, double v) {
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(a, __double2hiint(v)),
+                            __builtin_amdgcn_ds_bpermute(a, __double2loint(v)));
 }
 
 __device__ __forceinline__ float uniform_read(float v, int src) {

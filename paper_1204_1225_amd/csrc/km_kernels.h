@@ -13,6 +13,7 @@ struct TileShape {
     int depth_slots;    // KS: 16-depth slots per lane
     int lds_budget;
     int max_quads;      // demigrate: at most 4 * max_quads traces per workgroup (0: no cap)
+    int trace_parts;    // migrate: wavefronts that share one set of columns, each taking 1 / trace_parts of the traces
 };
 
 // Launch with `lds` bytes of dynamic LDS (raising the kernel's limit first
@@ -29,17 +30,26 @@ inline hipError_t launch_with_lds(Kernel kernel, dim3 grid, dim3 block, size_t l
 }
 
 // LDS of a migrate workgroup: the staged time windows (cap floats), per
-// block slot the trace geometry and window record (8 words), the chunk's
+// block slot the trace geometry, window record and bounds (12 words), the chunk's
 // aperture table (16 * ks floats), the column tile's bounding box (4 floats
-// per wavefront, at most 16 wavefronts), one pass's candidates (6 words
-// each, at most 64) and the anti-alias table 1 / n^2.
+// per wavefront, at most 16 wavefronts), two passes' candidates (1 word
+// each, at most 64), the anti-alias table 1 / n^2 and the list of near traces
+// (32 counts, list_cap entries).
 constexpr int kBoxFloats = 64;
 constexpr int kCandMax = 64;
-inline size_t migrate_lds_words(int cap, int tb, int ks) {
-    return static_cast<size_t>(cap) + static_cast<size_t>(8) * tb + static_cast<size_t>(16) * ks + kBoxFloats +
-           static_cast<size_t>(6) * kCandMax + ((kAAMaxHalf + 2 + 3) & ~3);
+constexpr int kWindowBias = 256;  // windows start at -256 or later
+constexpr int kInvSqFloats = (kAAMaxHalf + 2 + 3) & ~3;
+inline size_t migrate_lds_words(int cap, int tb, int ks, int list_cap) {
+    return static_cast<size_t>(cap) + static_cast<size_t>(12) * tb + static_cast<size_t>(16) * ks + kBoxFloats +
+           static_cast<size_t>(2) * kCandMax + kInvSqFloats + 32 + static_cast<size_t>(list_cap);
 }
-inline size_t lds_bytes(const Params& P, int ks) { return migrate_lds_words(P.cap, P.tb, ks) * sizeof(float); }
+inline size_t lds_bytes(const Params& P, int ks) {
+    return migrate_lds_words(P.cap, P.tb, ks, P.list_cap) * sizeof(float);
+}
+// Threads of a migrate workgroup that list near traces, one trace each per
+// pass (fewer where list_cap is less); the shortest list.
+constexpr int kListMin = 128;
+constexpr int list_threads(int waves) { return waves * kLanes < 512 ? waves * kLanes : 512; }
 
 // Demigrate workgroups keep their rows as float64 next to the staged geometry
 // (and the anti-alias table 1 / n^2).
@@ -78,7 +88,7 @@ hipError_t launch_fir(const float* in, int64_t in_stride, float* out, int64_t ou
 hipError_t launch_count(const Params& P, unsigned long long* counts, hipStream_t s);
 hipError_t launch_dot_f64(const float* a, const float* b, int64_t n, double* out, hipStream_t s);
 hipError_t launch_axpby(float alpha, const float* x, float beta, float* y, int64_t n, hipStream_t s);
-hipError_t launch_item_costs(const Params& P, int shape_ks, int cols_per_tile, unsigned long long* costs,
+hipError_t launch_item_costs(const Params& P, int cols_per_tile, unsigned long long* costs,
                              hipStream_t s);
 hipError_t launch_reset_counter(unsigned int* counter, hipStream_t s);
 hipError_t launch_probe(int kind, int n_waves, int iters, float* sink, hipStream_t s);

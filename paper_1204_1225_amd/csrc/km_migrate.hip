@@ -2,22 +2,36 @@
 //
 // Workgroup = (offset bin b, column tile, depth chunk).  Each wavefront keeps
 // CWQ groups of 4 image columns x (16 * KS) depths of float32 accumulators
-// in registers; the traces of bin b stream through LDS in blocks.  A trace
-// enters a block only if it can have a pair inside the aperture of the tile
-// and chunk, and only the time window its pairs can read is staged (the
-// double-square-root time grows with the squared leg lengths, so the window
-// follows from the tile's bounding box and the chunk's tables).  For every
-// column group the wavefront computes the two squared leg lengths of 16
-// traces at once (lane = (column, trace)), hands them to the depth lanes
-// through the LDS crossbar, derives from a ballot which 16-depth slots can
-// hold a pair inside the aperture, and evaluates those slots two at a time:
-// per lane two square roots, the sample index and fraction, one 8-byte LDS
-// read of the staged (sample, difference) pair, the interpolation, the weight
-// and the lane's aperture mask.  Table times and the anti-alias filter use
-// the same blocks with their own staged forms (plain samples; float64 double
-// running sums, one slot at a time).  With 16-bit traces the S16 kernels keep
-// the samples' 16-bit storage in LDS instead (packed pairs; single samples for
-// table times) and widen them on read.
+// in registers; the traces of bin b stream through LDS in blocks.  The traces
+// near the tile are listed first, a thread per trace; a listed trace enters a
+// block only if it can have a pair inside the aperture of the tile and chunk,
+// and only the time window its pairs can read is staged (the double-square-root
+// time grows with the squared leg lengths, so the window follows from the
+// tile's bounding box and the chunk's tables).  For every column group the
+// wavefront computes the two squared leg lengths of 16 traces at once (lane =
+// (column, trace)), hands them to the depth lanes through the LDS crossbar,
+// derives from ballots which 16-depth slots can hold a pair inside the aperture
+// and which are wholly inside, and evaluates those slots two at a time.  The
+// source leg's share of a pair is kept from trace to trace while the source
+// stays the same (SrcLeg); the receiver's costs one square root, the weight one
+// reciprocal, then the sample index and fraction, one 8-byte LDS read of the
+// staged (sample, difference) pair, the interpolation and, at the aperture's
+// edge, the lane's mask.  Table times and the anti-alias filter use the same
+// blocks with their own staged forms (plain samples; float64 double running
+// sums, one slot at a time).  With 16-bit traces the S16 kernels keep the
+// samples' 16-bit storage in LDS instead (packed pairs; single samples for table
+// times) and widen them on read.
+//
+// What bounds it: VALU issue (93 % of it on a survey of 200 000 traces over 16 x
+// 128 x 128 x 400 points, 5.2e11 pairs; transcendentals take 2.4 issue slots
+// each).  394 -> 316 ms there from keeping source legs, testing the aperture
+// only at its edge (13 instead of 15 VALU instructions per pair and lane),
+// reading a trace's row and clamp bounds by one broadcast, and staging 4
+// samples per lane; evaluating single slots where only one of a pair is inside
+// ran 396 ms (fewer instructions, less overlap).  On small images the wavefronts
+// are too few: see the tiles at the end of the file.
+#include <utility>
+
 #include "km_kernels.h"
 
 namespace km {
@@ -150,150 +164,212 @@ __device__ __forceinline__ void stage_window_i2(const Params& P, int64_t j, int 
     }
 }
 
-// Stage the window of samples lo .. lo + len - 1 of trace j as len - 1 pairs
-// dst[e] = (D[lo + e], D[lo + e + 1] - D[lo + e]): the interpolation then
-// reads one pair and needs one FMA.  One wavefront.
-__device__ __forceinline__ void stage_window(const Params& P, int64_t j, int lo, int len, float2* dst, int lane) {
-    const float sc = (P.dtype != F32 && P.scale) ? P.scale[j] : 1.0f;
-    for (int e0 = 0; e0 < len - 1; e0 += 2 * kLanes) {
-        float a[2], b[2];
+// Four consecutive samples of a row that may start at any sample.
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t ushort4_any __attribute__((ext_vector_type(4), aligned(2)));
+
+// The value of the next lane (lane 63: 0).
+__device__ __forceinline__ float next_lane(float v) { return dpp_f<0x130>(v); }
+
+// Samples e .. e + 3 of a window of len samples from sample lo of trace j, the
+// lane's share of a staging step (zero past the record's ends).
+__device__ __forceinline__ void load_quad(const Params& P, int64_t j, int lo, int len, int e, float* v) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int e = e0 + u * kLanes + lane;
-            a[u] = 0.0f;
-            b[u] = 0.0f;
-            if (e < len - 1) {
-                a[u] = trace_sample(P, j, lo + e, sc);
-                b[u] = trace_sample(P, j, lo + e + 1, sc);
-            }
+    for (int u = 0; u < 4; ++u) v[u] = 0.0f;
+    if (e >= len) return;
+    const float sc = (P.dtype != F32 && P.scale) ? P.scale[j] : 1.0f;
+    if (lo < 0 || lo + ((len - 1) & ~3) + 4 > P.nt) {  // some lane's 4 samples leave the record: checked loads
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = trace_sample(P, j, lo + e + u, sc);
+    } else if (P.dtype == F32) {
+        const float4_any w =
+            *reinterpret_cast<const float4_any*>(static_cast<const float*>(P.data) + j * P.stride + lo + e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = w[u];
+    } else {
+        const ushort4_any w =
+            *reinterpret_cast<const ushort4_any*>(static_cast<const uint16_t*>(P.data) + j * P.stride + lo + e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = widen16(w[u], P.dtype) * sc;
+    }
+}
+
+// Write the pairs e .. e + 3 of a window (lane 63 only hands its first sample down).
+__device__ __forceinline__ void store_quad(const float* v, int len, int e, float2* dst, int lane) {
+    const float nx = next_lane(v[0]);
+    if (e < len - 1 && lane < kLanes - 1) {
+        float4* o = reinterpret_cast<float4*>(dst + e);
+        o[0] = make_float4(v[0], v[1] - v[0], v[1], v[2] - v[1]);
+        o[1] = make_float4(v[2], v[3] - v[2], v[3], nx - v[3]);
+    }
+}
+
+// Stage the windows of the block's slots first, first + step, ... as pairs
+// dst[e] = (D[lo + e], D[lo + e + 1] - D[lo + e]): the interpolation then reads
+// one pair and needs one FMA.  One wavefront; a window is 16-byte aligned and
+// has room for its pair count rounded up to a multiple of 4.  A lane takes 4
+// consecutive samples (one load, two stores), and the loads of four traces are
+// in flight together.  With one sample per lane, checked and addressed one by
+// one, staging was a tenth of the VALU work of the survey's migration.
+__device__ __forceinline__ void stage_pairs(const Params& P, int64_t lo, const int4* sMeta, float* sTr, int nb,
+                                            int first, int step, int lane) {
+    constexpr int kAhead = 4;
+    for (int t0 = first; t0 < nb; t0 += kAhead * step) {
+        float v[kAhead][4];
+        int4 mt[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int t = t0 + u * step;
+            mt[u] = sMeta[min(t, nb - 1)];
+            // past the last slot: an empty window
+            if (t >= nb) mt[u].z = mt[u].y - 1;
+            load_quad(P, lo + mt[u].w, mt[u].y, mt[u].z - mt[u].y + 1, 4 * lane, v[u]);
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int e = e0 + u * kLanes + lane;
-            if (e < len - 1) dst[e] = make_float2(a[u], b[u] - a[u]);
+        for (int u = 0; u < kAhead; ++u) {
+            const int len = mt[u].z - mt[u].y + 1;
+            float2* dst = reinterpret_cast<float2*>(sTr + mt[u].x);
+            store_quad(v[u], len, 4 * lane, dst, lane);
+            for (int e0 = 4 * (kLanes - 1); e0 < len - 1; e0 += 4 * (kLanes - 1)) {  // windows of more than 252 pairs
+                float w[4];
+                load_quad(P, lo + mt[u].w, mt[u].y, len, e0 + 4 * lane, w);
+                store_quad(w, len, e0 + 4 * lane, dst, lane);
+            }
         }
     }
 }
 
-// Two slots (k, k + 1) of one (column group, trace) pairing.  MASKED: some
-// valid lane may be outside the aperture, so each value is kept only where
-// hmax <= the lane's aperture value; CLAMP: the time is clamped to the row.
-// R0, R1: the lanes' aperture values of the two slots (read only when MASKED).
-// row[i] = (D[i], D[i + 1] - D[i]) of the staged window.
-template <bool TF, int WK, bool MASKED, bool CLAMP>
-__device__ __forceinline__ void mig_pair(float A0, float B0, float A1, float B1, float hs2, float hr2, float hm,
-                                         const float2* row, float tfo, float wlo, float whi, float R0, float R1,
-                                         float& acc0, float& acc1) {
-    const Pair p0 = eval_pair<TF, WK, CLAMP>(A0, B0, hs2, hr2, tfo, wlo, whi);
-    const Pair p1 = eval_pair<TF, WK, CLAMP>(A1, B1, hs2, hr2, tfo, wlo, whi);
-    const float2 e0 = row[p0.i];
-    const float2 e1 = row[p1.i];
-    float v0 = fmaf(p0.f, e0.y, e0.x);
-    float v1 = fmaf(p1.f, e1.y, e1.x);
-    if (MASKED) {
-        v0 = (hm <= R0) ? v0 : 0.0f;
-        v1 = (hm <= R1) ? v1 : 0.0f;
+// What a pair needs of its source leg, per depth slot of one column group.
+// The traces of a bin come in shot order (the order every generator and most
+// acquisitions give), so consecutive traces of a block often share their
+// source: the source leg's share of a pair is evaluated when the source
+// changes and kept in registers until it changes again.  Each value is formed
+// by the operations the pair evaluation would use, so a pair has the same bits
+// whether its source leg was kept or not.
+//   square root        a = A + B h^2 and sqrt(a)
+//   anti-alias         sqrt(a) and its reciprocal
+//   extended           the leg time (float64) and the reciprocal square root seed
+//   tables             base and increment of the leg time, amplitude
+//   tables, extended   the leg time (float64), amplitude
+template <int KS, int TT, bool PX>
+struct SrcLeg {
+    float a[KS], s[KS];
+};
+template <int KS>
+struct SrcLeg<KS, TT_DSR, true> {
+    double t[KS];
+    float q[KS];
+};
+template <int KS>
+struct SrcLeg<KS, TT_TABLE, false> {
+    float base[KS], inc[KS], amp[KS];
+};
+template <int KS>
+struct SrcLeg<KS, TT_LTABLE, false> : SrcLeg<KS, TT_TABLE, false> {};
+template <int KS>
+struct SrcLeg<KS, TT_TABLE, true> {
+    double t[KS];
+    float amp[KS];
+};
+template <int KS>
+struct SrcLeg<KS, TT_LTABLE, true> : SrcLeg<KS, TT_TABLE, true> {};
+
+// Two slots of one (column group, trace) pairing with square-root times.
+// (sa, ss): the source leg of each slot; hr2: the receiver leg.  FULL: every
+// lane of both slots is inside the aperture (wavefront-uniform).
+template <bool TF, int WK>
+__device__ __forceinline__ void mig_pair(float A0, float B0, float A1, float B1, float sa0, float ss0, float sa1,
+                                         float ss1, float hr2, const float2* row, float tfo, float wlo, float whi,
+                                         float& v0, float& v1, float& r0, float& r1) {
+    const float ar0 = fmaf(B0, hr2, A0), ar1 = fmaf(B1, hr2, A1);
+    float w0 = ss0 + __builtin_amdgcn_sqrtf(ar0);
+    float w1 = ss1 + __builtin_amdgcn_sqrtf(ar1);
+    if (TF) {
+        w0 = w0 + tfo;
+        w1 = w1 + tfo;
     }
-    acc0 = (WK == W_COSCOS) ? fmaf(v0, p0.r, acc0) : acc0 + v0;
-    acc1 = (WK == W_COSCOS) ? fmaf(v1, p1.r, acc1) : acc1 + v1;
+    w0 = __builtin_amdgcn_fmed3f(w0, wlo, whi);
+    w1 = __builtin_amdgcn_fmed3f(w1, wlo, whi);
+    const float2 e0 = row[static_cast<int32_t>(w0)];
+    const float2 e1 = row[static_cast<int32_t>(w1)];
+    r0 = (WK == W_COSCOS) ? __builtin_amdgcn_rcpf(sa0 * ar0) : 1.0f;
+    r1 = (WK == W_COSCOS) ? __builtin_amdgcn_rcpf(sa1 * ar1) : 1.0f;
+    v0 = fmaf(__builtin_amdgcn_fractf(w0), e0.y, e0.x);
+    v1 = fmaf(__builtin_amdgcn_fractf(w1), e1.y, e1.x);
 }
 
 // mig_pair on a window staged as packed 16-bit pairs (stage_window_16p): the
 // pair is widened and interpolated, and the trace's scale joins the weight.
 template <bool TF, int WK, int DT>
-__device__ __forceinline__ void mig_pair16(float A0, float B0, float A1, float B1, float hs2, float hr2, float hm,
-                                           const uint32_t* row, float scl, float tfo, float wlo, float whi,
-                                           float R0, float R1, float& acc0, float& acc1) {
-    const Pair p0 = eval_pair<TF, WK, true>(A0, B0, hs2, hr2, tfo, wlo, whi);
-    const Pair p1 = eval_pair<TF, WK, true>(A1, B1, hs2, hr2, tfo, wlo, whi);
+__device__ __forceinline__ void mig_pair16(float A0, float B0, float A1, float B1, float sa0, float ss0, float sa1,
+                                           float ss1, float hr2, const uint32_t* row, float scl, float tfo, float wlo,
+                                           float whi, float& v0, float& v1, float& r0, float& r1) {
+    const float ar0 = fmaf(B0, hr2, A0), ar1 = fmaf(B1, hr2, A1);
+    float w0 = ss0 + __builtin_amdgcn_sqrtf(ar0);
+    float w1 = ss1 + __builtin_amdgcn_sqrtf(ar1);
+    if (TF) {
+        w0 = w0 + tfo;
+        w1 = w1 + tfo;
+    }
+    w0 = __builtin_amdgcn_fmed3f(w0, wlo, whi);
+    w1 = __builtin_amdgcn_fmed3f(w1, wlo, whi);
     float a0, b0, a1, b1;
-    widen_pair<DT>(row[p0.i], a0, b0);
-    widen_pair<DT>(row[p1.i], a1, b1);
-    float v0 = fmaf(p0.f, b0 - a0, a0);
-    float v1 = fmaf(p1.f, b1 - a1, a1);
-    v0 = (hm <= R0) ? v0 : 0.0f;
-    v1 = (hm <= R1) ? v1 : 0.0f;
-    acc0 = fmaf(v0, (WK == W_COSCOS) ? p0.r * scl : scl, acc0);
-    acc1 = fmaf(v1, (WK == W_COSCOS) ? p1.r * scl : scl, acc1);
+    widen_pair<DT>(row[static_cast<int32_t>(w0)], a0, b0);
+    widen_pair<DT>(row[static_cast<int32_t>(w1)], a1, b1);
+    r0 = (WK == W_COSCOS) ? __builtin_amdgcn_rcpf(sa0 * ar0) * scl : scl;
+    r1 = (WK == W_COSCOS) ? __builtin_amdgcn_rcpf(sa1 * ar1) * scl : scl;
+    v0 = fmaf(__builtin_amdgcn_fractf(w0), b0 - a0, a0);
+    v1 = fmaf(__builtin_amdgcn_fractf(w1), b1 - a1, a1);
 }
 
-// mig_pair with table traveltimes (W = A_s A_r with amplitude tables, else 1):
-// iz0, iz1 are the lane's depths of the two slots, clamped into the table.  LAT: laterally varying tables, C the
-// lane's column on the node grid.
-template <bool TF, bool MASKED, bool LAT>
-__device__ __forceinline__ void mig_pair_table(const Params& P, TLeg Ls, TLeg Lr, LCol C, int iz0, int iz1, float hm,
-                                               const float* row, float tfo, float wlo, float whi, float R0, float R1,
-                                               float& acc0, float& acc1) {
-    const Pair p0 = eval_pair_table<TF, true, LAT>(P, Ls, Lr, iz0, tfo, wlo, whi, C);
-    const Pair p1 = eval_pair_table<TF, true, LAT>(P, Ls, Lr, iz1, tfo, wlo, whi, C);
-    const float a0 = row[p0.i], b0 = row[p0.i + 1];
-    const float a1 = row[p1.i], b1 = row[p1.i + 1];
-    float v0 = fmaf(p0.f, b0 - a0, a0);
-    float v1 = fmaf(p1.f, b1 - a1, a1);
-    if (MASKED) {
+// Accumulate the values of slots k and k + 1.  Only where the slots are not
+// wholly inside the aperture (full: wavefront-uniform) is a lane's value
+// tested against its aperture (hm <= R) and dropped outside it.  Invalid lanes
+// of a full slot add a finite value that is never stored.
+template <int WK, int KS, bool RREG>
+__device__ __forceinline__ void mask_add2(const ChunkTables<KS>& T, const float* sR, uint32_t full, int k, int d,
+                                          float hm, float v0, float v1, float r0, float r1, float& acc0,
+                                          float& acc1) {
+    if (((full >> k) & 3u) != 3u) {
+        // a branch, not two selects per slot; the weights are formed before it
+        asm volatile("" : "+v"(r0), "+v"(r1));
+        const float R0 = RREG ? T.R[k] : sR[k * kGroup + d];
+        const float R1 = RREG ? T.R[k + 1] : sR[(k + 1) * kGroup + d];
         v0 = (hm <= R0) ? v0 : 0.0f;
         v1 = (hm <= R1) ? v1 : 0.0f;
     }
-    // r = 1 without amplitude tables: the same bits as acc + v
-    acc0 = fmaf(v0, p0.r, acc0);
-    acc1 = fmaf(v1, p1.r, acc1);
+    acc0 = (WK == W_COSCOS) ? fmaf(v0, r0, acc0) : acc0 + v0;
+    acc1 = (WK == W_COSCOS) ? fmaf(v1, r1, acc1) : acc1 + v1;
 }
 
-// mig_pair_table on a window staged as 16-bit values (stage_window_16): s is
-// the trace block's windows as words, rb the row's offset in 16-bit values.
-template <bool TF, bool LAT, int DT>
-__device__ __forceinline__ void mig_pair_table16(const Params& P, TLeg Ls, TLeg Lr, LCol C, int iz0, int iz1, float hm,
-                                                 const uint32_t* s, int rb, float scl, float tfo, float wlo, float whi,
-                                                 float R0, float R1, float& acc0, float& acc1) {
-    const Pair p0 = eval_pair_table<TF, true, LAT>(P, Ls, Lr, iz0, tfo, wlo, whi, C);
-    const Pair p1 = eval_pair_table<TF, true, LAT>(P, Ls, Lr, iz1, tfo, wlo, whi, C);
-    float a0, b0, a1, b1;
-    widen_pair<DT>(read_pair16(s, rb + p0.i), a0, b0);
-    widen_pair<DT>(read_pair16(s, rb + p1.i), a1, b1);
-    float v0 = fmaf(p0.f, b0 - a0, a0);
-    float v1 = fmaf(p1.f, b1 - a1, a1);
-    v0 = (hm <= R0) ? v0 : 0.0f;
-    v1 = (hm <= R1) ? v1 : 0.0f;
-    acc0 = fmaf(v0, p0.r * scl, acc0);
-    acc1 = fmaf(v1, p1.r * scl, acc1);
-}
-
-// One slot with the extended-precision time (eval_pair_ext): leg lengths in
-// float64, the clamp as integer bounds [ilo, ihi] (or float64 [wlo, whi] with
+// One slot with the extended-precision time: (ts, qs) the source leg's time
+// and seed, Hr the receiver's squared length, the clamp as integer bounds [ilo, ihi] (or float64 [wlo, whi] with
 // t_first).  One slot at a time: the float64 temporaries of two slots in
 // flight would cost more registers than the latency they hide.
 template <bool TF, int WK>
-__device__ __forceinline__ void mig_slot_ext(float A, float B, double Hs, double Hr, float hm, const float2* row,
-                                             double inv_dt, double tfo, int ilo, int ihi, double wlo, double whi,
-                                             float R, float& acc) {
+__device__ __forceinline__ void mig_slot_ext(float A, float B, double ts, float qs, double Hr, float hm,
+                                             const float2* row, double inv_dt, double tfo, int ilo, int ihi,
+                                             double wlo, double whi, float R, float& acc) {
     // keep the tables' float64 conversions inside the loop (hoisted, they
     // would hold two more registers per slot)
     asm volatile("" : "+v"(A), "+v"(B));
-    const PairX p = eval_pair_ext<TF, WK>(A, B, Hs, Hr, inv_dt, tfo, ilo, ihi, wlo, whi);
-    const float2 e = row[p.i];
-    float v = fmaf(p.f, e.y, e.x);
+    const LegTimeX r = leg_time_ext(A, B, Hr);
+    double w = (ts + r.t) * inv_dt;
+    int i;
+    if (TF) {
+        w = fmin(fmax(w + tfo, wlo), whi);
+        i = static_cast<int32_t>(w);
+    } else {
+        i = min(max(static_cast<int32_t>(w), ilo), ihi);
+    }
+    const float2 e = row[i];
+    float v = fmaf(static_cast<float>(__builtin_amdgcn_fract(w)), e.y, e.x);
     v = (hm <= R) ? v : 0.0f;
-    acc = (WK == W_COSCOS) ? fmaf(v, p.r, acc) : acc + v;
+    const float g = qs * r.q;
+    acc = (WK == W_COSCOS) ? fmaf(v, g * g, acc) : acc + v;
 }
 
-// mig_pair_table with extended legs (table_leg_ext).
-template <bool TF, bool LAT>
-__device__ __forceinline__ void mig_pair_table_ext(const Params& P, TLegX Ls, TLegX Lr, LCol C, int iz0, int iz1,
-                                                   float hm, const float* row, float wlo, float whi, float R0,
-                                                   float R1, float& acc0, float& acc1) {
-    const PairX p0 = eval_pair_table_ext<TF, LAT>(P, Ls, Lr, iz0, wlo, whi, C);
-    const PairX p1 = eval_pair_table_ext<TF, LAT>(P, Ls, Lr, iz1, wlo, whi, C);
-    const float a0 = row[p0.i], b0 = row[p0.i + 1];
-    const float a1 = row[p1.i], b1 = row[p1.i + 1];
-    float v0 = fmaf(p0.f, b0 - a0, a0);
-    float v1 = fmaf(p1.f, b1 - a1, a1);
-    v0 = (hm <= R0) ? v0 : 0.0f;
-    v1 = (hm <= R1) ? v1 : 0.0f;
-    acc0 = fmaf(v0, p0.r, acc0);
-    acc1 = fmaf(v1, p1.r, acc1);
-}
-
-// Two slots with the anti-alias triangle filter.  row[n] = I2 at window
+// The smoothed value of a pair with the anti-alias triangle filter.  row[n] = I2 at window
 // position n (staged by stage_window_i2): the smoothed sample at c is
 // alpha T_L(c) + beta T_{L+1}(c), T_L(c) = I2[c+L-1] - 2 I2[c-1] + I2[c-L-1],
 // read as five (n, n + 1) pairs for c = i and c = i + 1.
@@ -314,16 +390,97 @@ __device__ __forceinline__ float aa_value(const PairAA& p, const double* row) {
 }
 
 // One slot at a time (two in flight need more registers than the eight
-// float64 reads leave).
+// float64 reads leave).  (ss, is): square root of the source leg and its
+// reciprocal.
 template <bool TF, int WK>
-__device__ __forceinline__ void mig_slot_aa(float A, float B, float hs2, float hr2, float hm, const double* row,
-                                            float tfo, float wlo, float whi, float R, float dxs, float dys, float dxr,
-                                            float dyr, float adx, float ady, float lmax, const float* invsq,
-                                            float& acc) {
-    const PairAA p = eval_pair_aa<TF, WK>(A, B, hs2, hr2, tfo, wlo, whi, dxs, dys, dxr, dyr, adx, ady, lmax, invsq);
+__device__ __forceinline__ void mig_slot_aa(float A, float B, float ss, float is, float hr2, float hm,
+                                            const double* row, float tfo, float wlo, float whi, float R, float dxs,
+                                            float dys, float dxr, float dyr, float adx, float ady, float lmax,
+                                            const float* invsq, float& acc) {
+    const PairAA p = pair_aa<TF, WK>(A, B, ss, is, hr2, tfo, wlo, whi, dxs, dys, dxr, dyr, adx, ady, lmax, invsq);
     float v = aa_value<TF, WK>(p, row);
     v = (hm <= R) ? v : 0.0f;
     acc = (WK == W_COSCOS) ? fmaf(v, p.r, acc) : acc + v;
+}
+
+// The source legs of every slot from the leg's squared length (float32 and,
+// for the extended kernels, float64).  vd: byte offset of the lane's depth in
+// slot 0 of a table row.  Table slot pairs that no lane of the wavefront can use
+// are not read (a pair is evaluated whole, so both its slots are filled).
+template <int KS, int WK, int TT, bool PX>
+__device__ __forceinline__ void source_leg(const Params& P, const ChunkTables<KS>& T, float hs2, double Hs, LCol C,
+                                           int vd, SrcLeg<KS, TT, PX>& S) {
+    if constexpr (is_table(TT)) {
+        constexpr bool LAT = TT == TT_LTABLE;
+        const float hmin = uniform_f(rows_min(hs2));
+        const uint64_t any = __builtin_amdgcn_ballot_w64(hmin <= T.rhi);
+        if constexpr (PX) {
+            const TLegX L = table_leg_ext(P, Hs);
+            const int vb = 4 * ((LAT ? C.off : 0) + L.off) + vd;
+#pragma unroll
+            for (int k = 0; k < KS; ++k)
+                if ((any >> (k & ~1)) & 3ull) {
+                    S.t[k] = LAT ? ltable_time_ext_at(P, L.f, C, vb + 64 * k) : table_time_ext_at(P, L.f, vb + 64 * k);
+                    if (P.tamp) S.amp[k] = table_amp_at<LAT>(P, static_cast<float>(L.f), C, vb + 64 * k);
+                }
+        } else {
+            const TLeg L = table_leg(P, hs2);
+            const int vb = 4 * ((LAT ? C.off : 0) + L.off) + vd;
+#pragma unroll
+            for (int k = 0; k < KS; ++k)
+                if ((any >> (k & ~1)) & 3ull) {
+                    const TTime t = LAT ? ltable_time_at(P, L.f, C, vb + 64 * k) : table_time_at(P, L.f, vb + 64 * k);
+                    S.base[k] = t.base;
+                    S.inc[k] = t.inc;
+                    if (P.tamp) S.amp[k] = table_amp_at<LAT>(P, L.f, C, vb + 64 * k);
+                }
+        }
+    } else if constexpr (PX) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const LegTimeX l = leg_time_ext(T.A[k], T.B[k], Hs);
+            S.t[k] = l.t;
+            S.q[k] = l.q;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const float a = fmaf(T.B[k], hs2, T.A[k]);
+            const float r = __builtin_amdgcn_sqrtf(a);
+            S.a[k] = TT == TT_AA ? r : a;
+            S.s[k] = TT == TT_AA ? __builtin_amdgcn_rcpf(r) : r;
+        }
+    }
+}
+
+// A pair with table times, the source leg's share kept: time and (with
+// amplitude tables) weight at the table byte offset vb of the receiver leg.
+template <bool TF, bool LAT>
+__device__ __forceinline__ Pair pair_table(const Params& P, TTime ts, float as, float fr, int vb, float wlo, float whi,
+                                           LCol C) {
+    double w = pair_time(P, ts, LAT ? ltable_time_at(P, fr, C, vb) : table_time_at(P, fr, vb));
+    if (TF) w = w + P.tf_off_d;
+    w = fmin(fmax(w, static_cast<double>(wlo)), static_cast<double>(whi));
+    Pair p;
+    p.i = static_cast<int32_t>(w);
+    p.f = static_cast<float>(w - static_cast<double>(p.i));
+    p.r = 1.0f;
+    if (P.tamp) p.r = as * table_amp_at<LAT>(P, fr, C, vb);
+    return p;
+}
+
+template <bool TF, bool LAT>
+__device__ __forceinline__ Pair pair_table_ext(const Params& P, double ts, float as, double fr, int vb, float wlo,
+                                               float whi, LCol C) {
+    double w = (ts + (LAT ? ltable_time_ext_at(P, fr, C, vb) : table_time_ext_at(P, fr, vb))) * P.inv_dt;
+    if (TF) w = w + P.tf_off_d;
+    w = fmin(fmax(w, static_cast<double>(wlo)), static_cast<double>(whi));
+    Pair p;
+    p.i = static_cast<int32_t>(w);
+    p.f = static_cast<float>(w - static_cast<double>(p.i));
+    p.r = 1.0f;
+    if (P.tamp) p.r = as * table_amp_at<LAT>(P, static_cast<float>(fr), C, vb);
+    return p;
 }
 
 // RREG: the masked slots take the lanes' aperture values from registers
@@ -334,10 +491,12 @@ __device__ __forceinline__ void mig_slot_aa(float A, float B, float hs2, float h
 // leg lengths then also reach the depth lanes in float64.
 //
 // LDS (lds_bytes): window storage [P.cap floats; a window of n samples takes
-// n - 1 pairs], per block slot the trace geometry (float4) and (float offset,
-// first sample, last sample, trace - bin start) (int4) [P.tb each], the aperture values [KS * 16], the tile box
-// [4 per wavefront] and the candidates of one pass [NW * 4 x (int2, float4)].
-template <int NW, int CWQ, int KS, bool TF, int WK, bool RREG, int TT = TT_DSR, bool PX = false, int S16 = 0>
+// n - 1 pairs, rounded up to whole quads], per block slot the trace geometry (float4) and (float offset,
+// first sample, last sample, trace - bin start) (int4) and (row offset, clamp
+// bounds, scale) (float4) [P.tb each], the aperture values [KS * 16], the tile box
+// [4 per wavefront], the candidates of two passes [2 x NW * 4], the
+// per-wavefront counts [2 x 16] and the list of near traces [P.list_cap].
+template <int NW, int CWQ, int KS, int TS, bool TF, int WK, bool RREG, int TT = TT_DSR, bool PX = false, int S16 = 0>
 __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, int zc, float* lds) {
     static_assert(!(PX && TT == TT_AA), "no extended-precision anti-alias kernels");
     // S16: the 16-bit storage type (BF16 or F16) staged as it is, 0 for float staging
@@ -346,10 +505,14 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
     constexpr int NG = NW * kGroupsPerWave;  // candidate traces per pass: one per 16-lane group
     static_assert(NG <= kLanes && NW <= kBoxFloats / 4, "at most 16 wavefronts");
     const int lane = threadIdx.x & (kLanes - 1);
-    const int wave = threadIdx.x / kLanes;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    // column wavefront and trace part of this wavefront
+    constexpr int NC = NW / TS;
+    const int cw = wave % NC, part = wave / NC;
     const int g = lane / kGroup, d = lane % kGroup;
     const int ncol = P.nx * P.ny;
-    const int z0 = chunk_z0<false>(P.nz, zc, P.n_zchunks, KS * kGroup);
+    const int z0 = zc * P.zspan;
+    const int z1 = min(z0 + P.zspan, P.nz);  // end of the chunk's depths
     const int nt = P.nt;
     // staged-row index of sample k is k + koff (eval_pair adds kLead with t_first)
     const int koff = TF ? kLead : 0;
@@ -368,37 +531,23 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
     float* sTr = lds;                                                    // [cap]
     float4* sGeo = reinterpret_cast<float4*>(lds + P.cap);               // [tb]
     int4* sMeta = reinterpret_cast<int4*>(lds + P.cap + 4 * P.tb);       // [tb]
-    float* sR = lds + P.cap + 8 * P.tb;                                  // [KS * 16]
+    float4* sBnd = reinterpret_cast<float4*>(lds + P.cap + 8 * P.tb);    // [tb]
+    float* sR = lds + P.cap + 12 * P.tb;                                 // [KS * 16]
     float* sBox = sR + KS * kGroup;                                      // [kBoxFloats]
-    int2* sCand = reinterpret_cast<int2*>(sBox + kBoxFloats);            // [kCandMax]
-    float4* sCandGeo = reinterpret_cast<float4*>(sBox + kBoxFloats + 2 * kCandMax);  // [kCandMax]
-    float* sInvSq = sBox + kBoxFloats + 6 * kCandMax;                    // [kAAMaxHalf + 2]: 1 / n^2
+    uint32_t* sCand = reinterpret_cast<uint32_t*>(sBox + kBoxFloats);    // [2][kCandMax]
+    float* sInvSq = sBox + kBoxFloats + 2 * kCandMax;                    // [kAAMaxHalf + 2]: 1 / n^2
+    int* sCnt = reinterpret_cast<int*>(sInvSq + kInvSqFloats);           // [2][16]
+    int* sList = sCnt + 32;                                              // [list_cap]
     if (AA)
         for (int t = threadIdx.x; t < kAAMaxHalf + 2; t += blockDim.x)
             sInvSq[t] = t > 0 ? 1.0f / static_cast<float>(t * t) : 0.0f;
 
     ChunkTables<KS> T;
-    load_chunk_tables<KS, 1, TT, PX>(P, z0, d, WK == W_COSCOS, T, sR);
+    load_chunk_tables<KS, 1, TT, PX>(P, z0, z1, d, WK == W_COSCOS, T, sR);
 
-    float px[CWQ], py[CWQ];
-    int colv[CWQ];
-#pragma unroll
-    for (int q = 0; q < CWQ; ++q) {
-        const int col = (tile * NW * CWQ + wave * CWQ + q) * kGroupsPerWave + g;
-        colv[q] = col;
-        px[q] = kFar;
-        py[q] = kFar;
-        if (col < ncol) {
-            px[q] = P.x[col % P.nx];
-            py[q] = P.y[col / P.nx];
-        }
-    }
-
-    // the lane's columns on the node grid of laterally varying tables
     constexpr bool LAT = TT == TT_LTABLE;
-    LCol lc[CWQ];
-#pragma unroll
-    for (int q = 0; q < CWQ; ++q) lc[q] = LAT ? lateral_col(P, px[q], py[q]) : LCol{0, 0.0f, 0.0f};
+    // first column of the wavefront's groups; group q's lane column is col0 + 4 q + g
+    const int col0 = (tile * NC + cw) * CWQ * kGroupsPerWave;
 
     float acc[CWQ][KS];
 #pragma unroll
@@ -406,8 +555,8 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
 #pragma unroll
         for (int k = 0; k < KS; ++k) acc[q][k] = 0.0f;
 
-    const int64_t lo = lower_bound_bin(P.bin, P.n_traces, b);
-    const int64_t hi = lower_bound_bin(P.bin, P.n_traces, b + 1);
+    int64_t lo, hi;
+    bin_range(P.bin, P.n_traces, b, lo, hi);
     const float tfo = P.tf_off;
     const double tfod = P.tf_off_d;
 
@@ -419,11 +568,13 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
         float bx0 = __builtin_inff(), bx1 = -__builtin_inff(), by0 = __builtin_inff(), by1 = -__builtin_inff();
 #pragma unroll
         for (int q = 0; q < CWQ; ++q) {
-            if (colv[q] < ncol) {
-                bx0 = fminf(bx0, px[q]);
-                bx1 = fmaxf(bx1, px[q]);
-                by0 = fminf(by0, py[q]);
-                by1 = fmaxf(by1, py[q]);
+            const int col = col0 + kGroupsPerWave * q + g;
+            if (col < ncol) {
+                const float x = P.x[col % P.nx], y = P.y[col / P.nx];
+                bx0 = fminf(bx0, x);
+                bx1 = fmaxf(bx1, x);
+                by0 = fminf(by0, y);
+                by1 = fmaxf(by1, y);
             }
         }
         bx0 = wave_min(bx0);
@@ -461,293 +612,354 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
     const bool windows = TT == TT_DSR && __builtin_amdgcn_ballot_w64(!mono_lane) == 0;
     const int first_lo = TF ? -1 : 0;  // lowest staged sample (t_first = 0 gives u >= 0)
 
+    // The near traces (source and receiver within reach of the box) of the bin
+    // are listed first, one thread per trace, and only those are examined
+    // further: list entries lp .. nl - 1 are waiting, traces from jn on are
+    // not listed yet.  Every wavefront holds the same lp, nl, jn.
     int64_t jn = (T.rmax >= 0.0f) ? lo : hi;
-    while (jn < hi) {
-        // ---- Build a block: passes of NG candidates; candidate gi is trace jn + gi,
-        // evaluated by the 16 lanes of group gi.  Its window [wl, wl + len) of
+    int nl = 0, lp = 0, cpar = 0, cpass = 0;
+    const int nf = min(list_threads(NW), P.list_cap);  // threads that list, one trace each per pass
+    for (;;) {
+        // ---- Build a block: passes of NG candidates (list entries lp ...), each
+        // evaluated by the 16 lanes of one group.  Its window [wl, wl + len) of
         // samples covers, with a 2-sample margin, every time of a pair inside the
         // aperture: over the chunk's depths that can hold such a pair, the time at
         // the box's nearest distances bounds it from below, the time at the
         // farthest distances (capped at the depth's aperture) from above.
         int nb = 0, used = 0;
         for (;;) {
+            if (lp == nl) {
+                // list more near traces, in trace order, as long as a pass of nf fits; the
+                // old entries' readers are behind the first barrier
+                lp = 0;
+                nl = 0;
+                while (nl + nf <= P.list_cap && jn < hi) {
+                    const int tid = fresh_v(threadIdx.x);
+                    const int64_t j = jn + tid;
+                    bool near = false;
+                    if (j < hi && tid < nf) {
+                        const float ls = box_dist2(P.src[2 * j], P.src[2 * j + 1], bx0, bx1, by0, by1);
+                        const float lr = box_dist2(P.rec[2 * j], P.rec[2 * j + 1], bx0, bx1, by0, by1);
+                        near = fmaxf(ls, lr) <= reach;
+                    }
+                    const uint64_t m = __builtin_amdgcn_ballot_w64(near);
+                    int* cnt = sCnt + 16 * cpar;  // the two halves alternate: one barrier per pass
+                    cpar ^= 1;
+                    if (lane == 0) cnt[wave] = __builtin_popcountll(m);
+                    __syncthreads();
+                    int before = 0, total = 0;
+                    for (int w = 0; w < NW; ++w) {
+                        const int c = cnt[w];
+                        before += w < wave ? c : 0;
+                        total += c;
+                    }
+                    if (near)
+                        sList[nl + before + __builtin_popcountll(m & ((1ull << lane) - 1ull))] =
+                            static_cast<int>(j - lo);
+                    nl += __builtin_amdgcn_readfirstlane(total);
+                    jn += nf;
+                }
+                if (nl == 0) break;
+                __syncthreads();  // the list
+            }
             const int gi = wave * kGroupsPerWave + g;
-            const int64_t j = jn + gi;
+            const int nc = min(NG, nl - lp);  // candidates of this pass
             int wl = 0, len = 0;
             float4 sr = make_float4(kFar, kFar, kFar, kFar);
-            if (j < hi) {
+            if (gi < nc) {
+                const int64_t j = lo + sList[lp + gi];
                 sr = make_float4(P.src[2 * j], P.src[2 * j + 1], P.rec[2 * j], P.rec[2 * j + 1]);
-                const float ls = box_dist2(sr.x, sr.y, bx0, bx1, by0, by1);
-                const float lr = box_dist2(sr.z, sr.w, bx0, bx1, by0, by1);
-                const float m = fmaxf(ls, lr);
-                if (m <= reach) {
-                    wl = first_lo;
-                    len = nt + 2 - first_lo;  // samples first_lo .. nt + 1
-                    if (AA) {
-                        // positions -(2 lmax + 4) .. nt + 2 lmax + 4: every clamped sample's reads
-                        wl = -(2 * lmax + 4);
-                        len = nt + 4 * lmax + 9;
+                wl = first_lo;
+                len = nt + 2 - first_lo;  // samples first_lo .. nt + 1
+                if (AA) {
+                    // positions -(2 lmax + 4) .. nt + 2 lmax + 4: every clamped sample's reads
+                    wl = -(2 * lmax + 4);
+                    len = nt + 4 * lmax + 9;
+                }
+                if (windows) {
+                    const float ls = box_dist2(sr.x, sr.y, bx0, bx1, by0, by1);
+                    const float lr = box_dist2(sr.z, sr.w, bx0, bx1, by0, by1);
+                    const float m = fmaxf(ls, lr);
+                    const float ms = box_far2(sr.x, sr.y, bx0, bx1, by0, by1);
+                    const float mr = box_far2(sr.z, sr.w, bx0, bx1, by0, by1);
+                    float umin = __builtin_inff(), umax = -__builtin_inff();
+                    bool any = false, bad = false;
+#pragma unroll
+                    for (int k = 0; k < KS; ++k) {
+                        const float R = RREG ? T.R[k] : sR[k * kGroup + d];
+                        if (m <= R) {
+                            const float a = __builtin_amdgcn_sqrtf(fmaf(T.B[k], ls, T.A[k])) +
+                                            __builtin_amdgcn_sqrtf(fmaf(T.B[k], lr, T.A[k]));
+                            const float c = __builtin_amdgcn_sqrtf(fmaf(T.B[k], fminf(ms, R), T.A[k])) +
+                                            __builtin_amdgcn_sqrtf(fmaf(T.B[k], fminf(mr, R), T.A[k]));
+                            any = true;
+                            bad = bad || !(a == a && c == c);
+                            umin = fminf(umin, a);
+                            umax = fmaxf(umax, c);
+                        }
                     }
-                    if (windows) {
-                        const float ms = box_far2(sr.x, sr.y, bx0, bx1, by0, by1);
-                        const float mr = box_far2(sr.z, sr.w, bx0, bx1, by0, by1);
-                        float umin = __builtin_inff(), umax = -__builtin_inff();
-                        bool any = false, bad = false;
-#pragma unroll
-                        for (int k = 0; k < KS; ++k) {
-                            const float R = RREG ? T.R[k] : sR[k * kGroup + d];
-                            if (m <= R) {
-                                const float a = __builtin_amdgcn_sqrtf(fmaf(T.B[k], ls, T.A[k])) +
-                                                __builtin_amdgcn_sqrtf(fmaf(T.B[k], lr, T.A[k]));
-                                const float c = __builtin_amdgcn_sqrtf(fmaf(T.B[k], fminf(ms, R), T.A[k])) +
-                                                __builtin_amdgcn_sqrtf(fmaf(T.B[k], fminf(mr, R), T.A[k]));
-                                any = true;
-                                bad = bad || !(a == a && c == c);
-                                umin = fminf(umin, a);
-                                umax = fmaxf(umax, c);
-                            }
+                    umin = group_min(umin);
+                    umax = group_max(umax);
+                    if (PX) {  // physical tables: seconds -> samples (a monotone rounding)
+                        const float sc = static_cast<float>(P.inv_dt);
+                        umin = umin * sc;
+                        umax = umax * sc;
+                    }
+                    const uint32_t gany = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(any) >> (kGroup * g)) & 0xFFFFu;
+                    const uint32_t gbad = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(bad) >> (kGroup * g)) & 0xFFFFu;
+                    if (!gany) {
+                        len = 0;  // no depth of the chunk can hold a pair
+                    } else if (!gbad) {
+                        if (TF) {
+                            umin = umin + tfo;
+                            umax = umax + tfo;
                         }
-#pragma unroll
-                        for (int off = 1; off < kGroup; off <<= 1) {
-                            umin = fminf(umin, __shfl_xor(umin, off, kLanes));
-                            umax = fmaxf(umax, __shfl_xor(umax, off, kLanes));
-                        }
-                        if (PX) {  // physical tables: seconds -> samples (a monotone rounding)
-                            const float sc = static_cast<float>(P.inv_dt);
-                            umin = umin * sc;
-                            umax = umax * sc;
-                        }
-                        const uint32_t gany = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(any) >> (kGroup * g)) & 0xFFFFu;
-                        const uint32_t gbad = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(bad) >> (kGroup * g)) & 0xFFFFu;
-                        if (!gany) {
-                            len = 0;  // no depth of the chunk can hold a pair
-                        } else if (!gbad) {
-                            if (TF) {
-                                umin = umin + tfo;
-                                umax = umax + tfo;
-                            }
-                            // sample indices, clamped before conversion
-                            const float clo = -static_cast<float>(2 * lmax + 16);
-                            const float chi = static_cast<float>(nt + 2 * lmax + 16);
-                            const int fmin = static_cast<int>(floorf(fminf(fmaxf(umin, clo), chi))) - koff;
-                            const int fmax = static_cast<int>(floorf(fminf(fmaxf(umax, clo), chi))) - koff;
-                            if (AA) {
-                                // reads reach lmax + 2 around the sample; the clamp range
-                                // [wl + lmax + 2, wh - lmax - 2] must hold the pairs' samples
-                                const int a0 = max(fmin - lmax - 4, -(2 * lmax + 4));
-                                const int a1 = min(fmax + lmax + 4, nt + 2 * lmax + 4);
-                                if (a0 + lmax + 2 > a1 - lmax - 2) {
-                                    len = 0;  // every triangle lies outside the record
-                                } else {
-                                    wl = a0;
-                                    len = a1 - a0 + 1;
-                                }
-                            } else if (fmin - 2 > nt - 1 || fmax + 3 < 0) {
-                                len = 0;  // every such time reads zeros: nothing to add
+                        // sample indices, clamped before conversion
+                        const float clo = -static_cast<float>(2 * lmax + 16);
+                        const float chi = static_cast<float>(nt + 2 * lmax + 16);
+                        const int fmin = static_cast<int>(floorf(fminf(fmaxf(umin, clo), chi))) - koff;
+                        const int fmax = static_cast<int>(floorf(fminf(fmaxf(umax, clo), chi))) - koff;
+                        if (AA) {
+                            // reads reach lmax + 2 around the sample; the clamp range
+                            // [wl + lmax + 2, wh - lmax - 2] must hold the pairs' samples
+                            const int a0 = max(fmin - lmax - 4, -(2 * lmax + 4));
+                            const int a1 = min(fmax + lmax + 4, nt + 2 * lmax + 4);
+                            if (a0 + lmax + 2 > a1 - lmax - 2) {
+                                len = 0;  // every triangle lies outside the record
                             } else {
-                                wl = max(fmin - 2, first_lo);
-                                len = max(min(fmax + 3, nt + 1) - wl + 1, 2);
+                                wl = a0;
+                                len = a1 - a0 + 1;
                             }
+                        } else if (fmin - 2 > nt - 1 || fmax + 3 < 0) {
+                            len = 0;  // every such time reads zeros: nothing to add
+                        } else {
+                            wl = max(fmin - 2, first_lo);
+                            len = max(min(fmax + 3, nt + 1) - wl + 1, 2);
                         }
                     }
                 }
             }
-            __syncthreads();  // the previous pass (or block) is done with the candidates and rows
-            if (d == 0) {
-                sCand[gi] = make_int2(wl, len);
-                sCandGeo[gi] = sr;
-            }
+            // window start and length, 16 bits each (records of at most 20000 samples); the
+            // two halves alternate, so that one barrier per pass is enough (it also
+            // stands between the last block's readers and the next writes of its slots)
+            uint32_t* cand = sCand + kCandMax * cpass;
+            cpass ^= 1;
+            if (d == 0) cand[gi] = static_cast<uint32_t>(wl + kWindowBias) | (static_cast<uint32_t>(len) << 16);
             __syncthreads();
             // Every wavefront takes the same decision: candidates 0 .. k - 1 join the
             // block (the others do not fit and open the next one).
             int clen = 0, cwl = 0, cn = 0;  // LDS floats of the candidate's window, its first and number of samples
-            if (lane < NG) {
-                const int2 c = sCand[lane];
-                cwl = c.x;
-                cn = c.y;
-                clen = c.y > 0 ? (AA ? 2 * c.y : T16 ? (c.y + 1) / 2 : P16 ? c.y - 1 : PAIRS ? 2 * (c.y - 1) : c.y)
-                               : 0;
+            if (lane < nc) {
+                const uint32_t c = cand[lane];
+                cwl = static_cast<int>(c & 0xFFFFu) - kWindowBias;
+                cn = static_cast<int>(c >> 16);
+                clen = cn > 0 ? (AA      ? 2 * cn
+                                 : T16   ? (cn + 1) / 2
+                                 : P16   ? cn - 1
+                                 : PAIRS ? 2 * ((cn + 2) & ~3)  // whole quads of pairs: stage_pairs
+                                         : cn)
+                              : 0;
             }
-            int plen = clen, pcnt = clen > 0 ? 1 : 0;  // inclusive prefix sums
-#pragma unroll
-            for (int off = 1; off < NG; off <<= 1) {
-                const int tl = __shfl_up(plen, off, kLanes), tc = __shfl_up(pcnt, off, kLanes);
-                if (lane >= off) {
-                    plen += tl;
-                    pcnt += tc;
-                }
-            }
+            const int plen = wave_scan(clen), pcnt = wave_scan(clen > 0 ? 1 : 0);  // inclusive prefix sums
             const bool fits = used + plen <= P.cap && nb + pcnt <= P.tb;
-            const uint64_t nofit = __builtin_amdgcn_ballot_w64(lane < NG && !fits);
-            const int k = nofit ? static_cast<int>(__builtin_ctzll(nofit)) : NG;
+            const uint64_t nofit = __builtin_amdgcn_ballot_w64(lane < nc && !fits);
+            const int k = nofit ? static_cast<int>(__builtin_ctzll(nofit)) : nc;
             if (wave == 0 && lane < k && clen > 0) {
                 const int slot = nb + pcnt - 1;
-                sGeo[slot] = sCandGeo[lane];
-                sMeta[slot] = make_int4(used + plen - clen, cwl, cwl + cn - 1, static_cast<int>(jn + lane - lo));
+                const int jl = sList[lp + lane];
+                const int64_t j = lo + jl;
+                sGeo[slot] = make_float4(P.src[2 * j], P.src[2 * j + 1], P.rec[2 * j], P.rec[2 * j + 1]);
+                const int off = used + plen - clen, cwh = cwl + cn - 1;  // window samples cwl .. cwh
+                sMeta[slot] = make_int4(off, cwl, cwh, jl);
+                // the row's offset (position of sample 0 plus koff), the clamp bounds and,
+                // with 16-bit staging, the trace's scale (applied per pair with the weight)
+                sBnd[slot] = make_float4(
+                    __int_as_float((PAIRS || AA ? off / 2 : T16 ? 2 * off : off) - cwl - koff),
+                    static_cast<float>(cwl + koff + (AA ? lmax + 2 : 0)),
+                    static_cast<float>(cwh - 1 + koff - (AA ? lmax + 1 : 0)), (S16 && P.scale) ? P.scale[j] : 1.0f);
             }
             if (k > 0) {
                 nb += __builtin_amdgcn_readlane(pcnt, k - 1);
                 used += __builtin_amdgcn_readlane(plen, k - 1);
             }
-            jn += k;
-            if (k < NG || jn >= hi) break;
+            lp += k;
+            if (k < nc) break;
         }
-        if (nb == 0) continue;  // only when the bin is exhausted
-        __syncthreads();        // the block's slots
-        for (int t = wave; t < nb; t += NW) {
+        if (nb == 0) break;  // the bin is exhausted (a block that breaks off full holds a trace)
+        __syncthreads();     // the block's slots
+        const int sl = fresh_v(lane);
+        if (PAIRS) stage_pairs(P, lo, sMeta, sTr, nb, wave, NW, sl);
+        for (int t = PAIRS ? nb : wave; t < nb; t += NW) {
             const int4 mt = sMeta[t];
-            if (AA) stage_window_i2(P, lo + mt.w, mt.y, mt.z - mt.y + 1, reinterpret_cast<double*>(sTr + mt.x), lane);
-            else if (T16) stage_window_16(P, lo + mt.w, mt.y, mt.z - mt.y + 1, reinterpret_cast<uint16_t*>(sTr + mt.x), lane);
-            else if (P16) stage_window_16p(P, lo + mt.w, mt.y, mt.z - mt.y + 1, reinterpret_cast<uint32_t*>(sTr + mt.x), lane);
-            else if (PAIRS) stage_window(P, lo + mt.w, mt.y, mt.z - mt.y + 1, reinterpret_cast<float2*>(sTr + mt.x), lane);
-            else stage_window_f(P, lo + mt.w, mt.y, mt.z - mt.y + 1, sTr + mt.x, lane);
+            if (AA) stage_window_i2(P, lo + mt.w, mt.y, mt.z - mt.y + 1, reinterpret_cast<double*>(sTr + mt.x), sl);
+            else if (T16) stage_window_16(P, lo + mt.w, mt.y, mt.z - mt.y + 1, reinterpret_cast<uint16_t*>(sTr + mt.x), sl);
+            else if (P16) stage_window_16p(P, lo + mt.w, mt.y, mt.z - mt.y + 1, reinterpret_cast<uint32_t*>(sTr + mt.x), sl);
+            else stage_window_f(P, lo + mt.w, mt.y, mt.z - mt.y + 1, sTr + mt.x, sl);
         }
         __syncthreads();
 
-        for (int t0 = 0; t0 < nb; t0 += kGroup) {
-            const int nbt = min(kGroup, nb - t0);
-            // lane (g, d): legs of column group member g and trace t0 + d; the
-            // trace's row offset and clamp bounds (window samples wl .. wh)
-            const int ts = min(t0 + d, nb - 1);
-            const float4 sr = sGeo[ts];
-            const int4 mt = sMeta[ts];
-            // in pairs / doubles / 16-bit samples / floats or packed 16-bit pairs
-            const int lrow = (PAIRS || AA ? mt.x / 2 : T16 ? 2 * mt.x : mt.x) - mt.y - koff;
-            // 16-bit staging: the trace's scale, applied per pair with the weight
-            const float lscl = (S16 && P.scale) ? P.scale[lo + mt.w] : 1.0f;
-            const float lwlo = static_cast<float>(mt.y + koff + (AA ? lmax + 2 : 0));
-            const float lwhi = static_cast<float>(mt.z - 1 + koff - (AA ? lmax + 1 : 0));
+        // Column group by column group over the block, so that one group's source
+        // legs (SrcLeg) live in registers from trace to trace.
 #pragma unroll
-            for (int q = 0; q < CWQ; ++q) {
-                const Legs Lp = legs(px[q], py[q], sr);
+        for (int q = 0; q < CWQ; ++q) {
+            // the lane's column of this group (looked up again for every block: the
+            // registers it would take are worth more than the few reads)
+            const int col = col0 + kGroupsPerWave * q + fresh_v(g);
+            const bool has = col < ncol;
+            const float px = has ? P.x[col % P.nx] : kFar, py = has ? P.y[col / P.nx] : kFar;
+            const LCol lc = LAT ? lateral_col(P, px, py) : LCol{0, 0.0f, 0.0f};
+            SrcLeg<KS, TT, PX> S;
+            float hs2 = 0.0f, dxs = 0.0f, dys = 0.0f;  // the kept source leg: squared length, components
+            // position of the source whose leg is kept (none yet: equal to nothing)
+            float curx = __builtin_nanf(""), cury = __builtin_nanf("");
+            for (int t0 = 0; t0 < nb; t0 += kGroup) {
+                const int nbt = min(kGroup, nb - t0);
+                // lane (g, d): legs of column group member g and trace t0 + d
+                const float4 sr = sGeo[min(t0 + d, nb - 1)];
+                const Legs Lp = legs(px, py, sr);
                 LegsX Lx{0.0, 0.0};
-                if (PX) Lx = legs_ext(px[q], py[q], sr);
-                // extremes of hmax over the four columns, per trace (lanes d, 16 + d, 32 + d, 48 + d)
-                float hmin4 = fminf(Lp.hmax, __shfl_xor(Lp.hmax, 16, kLanes));
-                hmin4 = fminf(hmin4, __shfl_xor(hmin4, 32, kLanes));
-                float hmax4 = fmaxf(Lp.hmax, __shfl_xor(Lp.hmax, 16, kLanes));
-                hmax4 = fmaxf(hmax4, __shfl_xor(hmax4, 32, kLanes));
-                uint64_t live = __builtin_amdgcn_ballot_w64(hmin4 <= T.rmax) & ((1ull << nbt) - 1ull);
+                if (PX) Lx = legs_ext(px, py, sr);
+                // traces that some column of the group can reach at some depth of the chunk
+                uint32_t live = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(rows_min(Lp.hmax) <= T.rmax)) &
+                                ((1u << nbt) - 1u);
+                // this wavefront's share of the traces (by the trace's place in the bin, so that the
+                // sums do not depend on where a block ends)
+                if (TS > 1)
+                    live &= static_cast<uint32_t>(
+                        __builtin_amdgcn_ballot_w64(sMeta[min(t0 + d, nb - 1)].w % TS == part));
                 if (!live) continue;
-                // The legs of trace t reach the depth lanes through the LDS crossbar; the
-                // next live trace's are requested before trace t is evaluated.
-                int t = __builtin_ctzll(live);
-                live &= live - 1;
-                // (The upper clamp bound also comes through the crossbar, as a vector
-                // register: a clamp with two scalar bounds costs a move per pair.)
-                float hs2n = lane_read(Lp.hs2, (lane & ~(kGroup - 1)) | t);
-                float hr2n = lane_read(Lp.hr2, (lane & ~(kGroup - 1)) | t);
-                float whin = lane_read(lwhi, t);
-                double Hsn = 0.0, Hrn = 0.0;
-                if (PX) {
-                    Hsn = lane_read_d(Lx.hs2, (lane & ~(kGroup - 1)) | t);
-                    Hrn = lane_read_d(Lx.hr2, (lane & ~(kGroup - 1)) | t);
-                }
+                // bit t: trace t0 + t has another source than the trace before it (t = 0: than the kept one)
+                const float ux = dpp_f<0x111>(sr.x), uy = dpp_f<0x111>(sr.y);
+                uint32_t fresh = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(
+                                     d == 0 ? !(sr.x == curx && sr.y == cury) : !(sr.x == ux && sr.y == uy))) & 0xFFFFu;
+                // The receiver leg of trace t reaches the depth lanes through the LDS
+                // crossbar; the next live trace's is requested before trace t is evaluated.
+                const int row4 = 4 * (lane & ~(kGroup - 1));  // crossbar address of the lane's row
+                int t = __builtin_ctz(live);
+                float hr2n = bperm_f(row4 | 4 * t, Lp.hr2);
+                double Hrn = 0.0;
+                if (PX) Hrn = bperm_d(row4 | 4 * t, Lx.hr2);
                 for (;;) {
                     const int tc = t;
-                    const float hs2 = hs2n, hr2 = hr2n, whi = whin;
-                    const double Hs = Hsn, Hr = Hrn;
+                    const float hr2 = hr2n;
+                    const double Hr = Hrn;
+                    // row offset, clamp bounds and scale of the trace, the same for every lane
+                    // (vector registers: a clamp with two scalar bounds costs a move per pair)
+                    const float4 bd = sBnd[t0 + tc];
+                    live ^= 1u << tc;
                     const bool more = live != 0;
                     if (more) {
-                        t = __builtin_ctzll(live);
-                        live &= live - 1;
-                        hs2n = lane_read(Lp.hs2, (lane & ~(kGroup - 1)) | t);
-                        hr2n = lane_read(Lp.hr2, (lane & ~(kGroup - 1)) | t);
-                        whin = lane_read(lwhi, t);
-                        if (PX) {
-                            Hsn = lane_read_d(Lx.hs2, (lane & ~(kGroup - 1)) | t);
-                            Hrn = lane_read_d(Lx.hr2, (lane & ~(kGroup - 1)) | t);
-                        }
+                        t = __builtin_ctz(live);
+                        hr2n = bperm_f(row4 | 4 * t, Lp.hr2);
+                        if (PX) Hrn = bperm_d(row4 | 4 * t, Lx.hr2);
                     }
-                    const float hmin = uniform_read(hmin4, tc);
-                    const float hmaxw = uniform_read(hmax4, tc);
-                    uint64_t any, full;
-                    slot_masks<KS>(T, hmin, hmaxw, any, full);
-                    (void)full;
+                    const uint32_t upto = (2u << tc) - 1u;
+                    if (fresh & upto) {
+                        fresh &= ~upto;
+                        curx = uniform_read(sr.x, tc);
+                        cury = uniform_read(sr.y, tc);
+                        hs2 = bperm_f(row4 | 4 * tc, Lp.hs2);
+                        if constexpr (AA) {
+                            dxs = px - curx;
+                            dys = py - cury;
+                        }
+                        double Hs = 0.0;
+                        if (PX) Hs = bperm_d(row4 | 4 * tc, Lx.hs2);
+                        source_leg<KS, WK, TT, PX>(P, T, hs2, Hs, lc, 4 * (z0 + d), S);
+                    }
+                    // max(hs2, hr2): one v_max (fmaxf would first quiet both inputs)
+                    float hm;
+                    asm("v_max_f32 %0, %1, %2" : "=v"(hm) : "v"(hs2), "v"(hr2));
+                    uint32_t any, full;
+                    slot_masks<KS>(T, hm, any, full);
                     if (!any) {
                         if (!more) break;
                         continue;
                     }
-                    const int rb = __builtin_amdgcn_readlane(lrow, tc);
-                    const float wlo = uniform_read(lwlo, tc);
-                    const float scl = S16 ? uniform_read(lscl, tc) : 1.0f;
-                    // max(hs2, hr2): one v_max (fmaxf would first quiet both inputs)
-                    float hm;
-                    asm("v_max_f32 %0, %1, %2" : "=v"(hm) : "v"(hs2), "v"(hr2));
-                    if (is_table(TT) && PX) {
-                        const TLegX Ls = table_leg_ext(P, Hs), Lr = table_leg_ext(P, Hr);
+                    // in pairs / doubles / 16-bit samples / floats or packed 16-bit pairs
+                    const int rb = __float_as_int(bd.x);
+                    const float wlo = bd.y, whi = bd.z, scl = bd.w;
+                    if constexpr (is_table(TT) && PX) {
+                        const TLegX Lr = table_leg_ext(P, Hr);
+                        const int vr = 4 * ((LAT ? lc.off : 0) + Lr.off + z0 + d);
+                        const float* row = sTr + rb;
 #pragma unroll
                         for (int k = 0; k < KS; k += 2) {
-                            if ((any >> k) & 3ull) {
-                                const int iz0 = min(max(z0 + k * kGroup + d, 0), P.nz - 1);
-                                const int iz1 = min(max(z0 + (k + 1) * kGroup + d, 0), P.nz - 1);
-                                const float R0 = RREG ? T.R[k] : sR[k * kGroup + d];
-                                const float R1 = RREG ? T.R[k + 1] : sR[(k + 1) * kGroup + d];
-                                mig_pair_table_ext<TF, LAT>(P, Ls, Lr, lc[q], iz0, iz1, hm, sTr + rb, wlo, whi, R0, R1,
-                                                            acc[q][k], acc[q][k + 1]);
+                            if ((any >> k) & 3u) {
+                                const Pair p0 = pair_table_ext<TF, LAT>(P, S.t[k], S.amp[k], Lr.f, vr + 64 * k, wlo, whi, lc);
+                                const Pair p1 = pair_table_ext<TF, LAT>(P, S.t[k + 1], S.amp[k + 1], Lr.f, vr + 64 * k + 64, wlo, whi, lc);
+                                const float a0 = row[p0.i], b0 = row[p0.i + 1];
+                                const float a1 = row[p1.i], b1 = row[p1.i + 1];
+                                mask_add2<W_COSCOS, KS, RREG>(T, sR, full, k, d, hm, fmaf(p0.f, b0 - a0, a0),
+                                                              fmaf(p1.f, b1 - a1, a1), p0.r, p1.r, acc[q][k], acc[q][k + 1]);
                             }
                         }
-                    } else if (is_table(TT)) {
-                        const TLeg Ls = table_leg(P, hs2), Lr = table_leg(P, hr2);
+                    } else if constexpr (is_table(TT)) {
+                        const TLeg Lr = table_leg(P, hr2);
+                        const int vr = 4 * ((LAT ? lc.off : 0) + Lr.off + z0 + d);
+                        const float* row = sTr + rb;
+                        const uint32_t* sw = reinterpret_cast<const uint32_t*>(sTr);
 #pragma unroll
                         for (int k = 0; k < KS; k += 2) {
-                            if ((any >> k) & 3ull) {
-                                const int iz0 = min(max(z0 + k * kGroup + d, 0), P.nz - 1);
-                                const int iz1 = min(max(z0 + (k + 1) * kGroup + d, 0), P.nz - 1);
-                                const float R0 = RREG ? T.R[k] : sR[k * kGroup + d];
-                                const float R1 = RREG ? T.R[k + 1] : sR[(k + 1) * kGroup + d];
-                                if (S16)
-                                    mig_pair_table16<TF, LAT, S16>(P, Ls, Lr, lc[q], iz0, iz1, hm,
-                                                                   reinterpret_cast<const uint32_t*>(sTr), rb, scl,
-                                                                   tfo, wlo, whi, R0, R1, acc[q][k], acc[q][k + 1]);
-                                else
-                                    mig_pair_table<TF, true, LAT>(P, Ls, Lr, lc[q], iz0, iz1, hm, sTr + rb, tfo, wlo,
-                                                                  whi, R0, R1, acc[q][k], acc[q][k + 1]);
+                            if ((any >> k) & 3u) {
+                                const Pair p0 = pair_table<TF, LAT>(P, TTime{S.base[k], S.inc[k]}, S.amp[k], Lr.f, vr + 64 * k, wlo, whi, lc);
+                                const Pair p1 = pair_table<TF, LAT>(P, TTime{S.base[k + 1], S.inc[k + 1]}, S.amp[k + 1], Lr.f, vr + 64 * k + 64, wlo, whi, lc);
+                                float a0, b0, a1, b1;
+                                if (S16) {
+                                    widen_pair<S16>(read_pair16(sw, rb + p0.i), a0, b0);
+                                    widen_pair<S16>(read_pair16(sw, rb + p1.i), a1, b1);
+                                } else {
+                                    a0 = row[p0.i], b0 = row[p0.i + 1];
+                                    a1 = row[p1.i], b1 = row[p1.i + 1];
+                                }
+                                mask_add2<W_COSCOS, KS, RREG>(T, sR, full, k, d, hm, fmaf(p0.f, b0 - a0, a0),
+                                                              fmaf(p1.f, b1 - a1, a1), S16 ? p0.r * scl : p0.r,
+                                                              S16 ? p1.r * scl : p1.r, acc[q][k], acc[q][k + 1]);
                             }
                         }
-                    } else if (AA) {
-                        // column minus source / receiver of trace tc, for the operator dip
-                        const float dxs = px[q] - uniform_read(sr.x, tc), dys = py[q] - uniform_read(sr.y, tc);
-                        const float dxr = px[q] - uniform_read(sr.z, tc), dyr = py[q] - uniform_read(sr.w, tc);
+                    } else if constexpr (AA) {
+                        // column minus receiver of trace tc, for the operator dip
+                        const float dxr = px - uniform_read(sr.z, tc), dyr = py - uniform_read(sr.w, tc);
                         const double* rowd = reinterpret_cast<const double*>(sTr) + rb;
 #pragma unroll
                         for (int k = 0; k < KS; ++k) {
-                            if ((any >> k) & 1ull) {
+                            if ((any >> k) & 1u) {
                                 const float R = RREG ? T.R[k] : sR[k * kGroup + d];
-                                mig_slot_aa<TF, WK>(T.A[k], T.B[k], hs2, hr2, hm, rowd, tfo, wlo, whi, R, dxs, dys, dxr,
-                                                    dyr, P.aa_dx, P.aa_dy, static_cast<float>(lmax), sInvSq,
-                                                    acc[q][k]);
+                                mig_slot_aa<TF, WK>(T.A[k], T.B[k], S.a[k], S.s[k], hr2, hm, rowd, tfo, wlo, whi, R,
+                                                    dxs, dys, dxr, dyr, P.aa_dx, P.aa_dy, static_cast<float>(lmax),
+                                                    sInvSq, acc[q][k]);
                             }
                         }
-                    } else if (PX) {
+                    } else if constexpr (PX) {
                         const int ilo = static_cast<int>(wlo), ihi = static_cast<int>(whi);
                         const double wlod = wlo, whid = whi;
+                        const float2* row = reinterpret_cast<const float2*>(sTr) + rb;
 #pragma unroll
                         for (int k = 0; k < KS; ++k) {
-                            if ((any >> k) & 1ull) {
+                            if ((any >> k) & 1u) {
                                 const float R = RREG ? T.R[k] : sR[k * kGroup + d];
-                                mig_slot_ext<TF, WK>(T.A[k], T.B[k], Hs, Hr, hm,
-                                                     reinterpret_cast<const float2*>(sTr) + rb, P.inv_dt, tfod, ilo,
+                                mig_slot_ext<TF, WK>(T.A[k], T.B[k], S.t[k], S.q[k], Hr, hm, row, P.inv_dt, tfod, ilo,
                                                      ihi, wlod, whid, R, acc[q][k]);
                             }
                         }
                     } else {
-                        // Every slot pair goes through the masked, clamped form: one code path
-                        // per pair measured faster than separate unmasked / unclamped variants
-                        // (their extra branches and code cost more than the masks they save).
 #pragma unroll
                         for (int k = 0; k < KS; k += 2) {
-                            if ((any >> k) & 3ull) {
-                                const float R0 = RREG ? T.R[k] : sR[k * kGroup + d];
-                                const float R1 = RREG ? T.R[k + 1] : sR[(k + 1) * kGroup + d];
-                                if (S16)
-                                    mig_pair16<TF, WK, S16>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], hs2, hr2, hm,
-                                                            reinterpret_cast<const uint32_t*>(sTr) + rb, scl, tfo,
-                                                       wlo, whi, R0, R1, acc[q][k], acc[q][k + 1]);
-                                else
-                                    mig_pair<TF, WK, true, true>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], hs2, hr2, hm,
-                                                                 reinterpret_cast<const float2*>(sTr) + rb,
-                                                                 tfo, wlo, whi, R0, R1, acc[q][k], acc[q][k + 1]);
+                            if ((any >> k) & 3u) {
+                                float v0, v1, r0, r1;
+                                if (S16) {
+                                    mig_pair16<TF, WK, S16>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], S.a[k], S.s[k],
+                                                            S.a[k + 1], S.s[k + 1], hr2,
+                                                            reinterpret_cast<const uint32_t*>(sTr) + rb, scl, tfo, wlo,
+                                                            whi, v0, v1, r0, r1);
+                                } else {
+                                    mig_pair<TF, WK>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], S.a[k], S.s[k],
+                                                     S.a[k + 1], S.s[k + 1], hr2,
+                                                     reinterpret_cast<const float2*>(sTr) + rb, tfo, wlo, whi, v0, v1,
+                                                     r0, r1);
+                                }
+                                mask_add2<S16 ? W_COSCOS : WK, KS, RREG>(T, sR, full, k, d, hm, v0, v1, r0, r1,
+                                                                         acc[q][k], acc[q][k + 1]);
                             }
                         }
                     }
@@ -757,15 +969,32 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
         }
     }
 
+    if (TS > 1) {
+        // the parts' sums through LDS (the window storage is free), added in part order
+        __syncthreads();
+        constexpr int kPart = NC * CWQ * KS * kLanes;
+        float* mine = sTr + cw * (CWQ * KS * kLanes) + lane;
+        if (part > 0)
+#pragma unroll
+            for (int e = 0; e < CWQ * KS; ++e) mine[(part - 1) * kPart + e * kLanes] = acc[e / KS][e % KS];
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int e = 0; e < CWQ * KS; ++e)
+#pragma unroll
+            for (int o = 0; o < TS - 1; ++o) acc[e / KS][e % KS] += mine[o * kPart + e * kLanes];
+    }
+
     float* img = P.image + static_cast<int64_t>(b) * ncol * P.nz;
 #pragma unroll
     for (int q = 0; q < CWQ; ++q) {
-        if (colv[q] >= ncol) continue;
-        float* colp = img + static_cast<int64_t>(colv[q]) * P.nz;
+        const int col = col0 + kGroupsPerWave * q + fresh_v(g);
+        if (col >= ncol) continue;
+        float* colp = img + static_cast<int64_t>(col) * P.nz;
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
             const int iz = z0 + k * kGroup + d;
-            if (iz >= 0 && iz < P.nz) {
+            if (iz < z1) {
                 const float fac = depth_factor<PX>(P, iz);
                 const float val = fac != 0.0f ? acc[q][k] * fac : 0.0f;
                 colp[iz] = P.accumulate ? colp[iz] + val : val;
@@ -776,35 +1005,39 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
 
 // Store zeros into a tile whose (column, trace) pairs are all outside the
 // aperture (known from the counting kernel): its image values are exactly 0.
-template <int NW, int CWQ, int KS>
+template <int NW, int CWQ, int KS, int TS>
 __device__ __forceinline__ void zero_tile(const Params& P, int b, int tile, int zc) {
     if (P.accumulate) return;
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = threadIdx.x / kLanes;
+    if (wave >= NW / TS) return;  // the column wavefronts
     const int g = lane / kGroup, d = lane % kGroup;
     const int ncol = P.nx * P.ny;
-    const int z0 = chunk_z0<false>(P.nz, zc, P.n_zchunks, KS * kGroup);
+    const int z0 = zc * P.zspan;
+    const int z1 = min(z0 + P.zspan, P.nz);  // end of the chunk's depths
     float* img = P.image + static_cast<int64_t>(b) * ncol * P.nz;
 #pragma unroll
     for (int q = 0; q < CWQ; ++q) {
-        const int col = (tile * NW * CWQ + wave * CWQ + q) * kGroupsPerWave + g;
+        const int col = ((tile * (NW / TS) + wave) * CWQ + q) * kGroupsPerWave + g;
         if (col >= ncol) continue;
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
             const int iz = z0 + k * kGroup + d;
-            if (iz >= 0 && iz < P.nz) img[static_cast<int64_t>(col) * P.nz + iz] = 0.0f;
+            if (iz < z1) img[static_cast<int64_t>(col) * P.nz + iz] = 0.0f;
         }
     }
 }
 
-// The extended-precision square-root kernels are held to 4 wavefronts per SIMD
-// (128 VGPRs, some spilled) so that two 8-wavefront workgroups share a CU:
-// 2.28 s against 3.29 s at their natural 165 VGPRs on the 3D survey.
-template <int NW, int CWQ, int KS, bool TF, int WK, int TT = TT_DSR, bool PX = false, int S16 = 0>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PX && TT == TT_DSR && KS <= 8 ? 4 : 1)))
+// Held to 4 wavefronts per SIMD (128 VGPRs; the 4-group shapes spill about 20,
+// outside the pair loops) so that two 8-wavefront workgroups share a CU: 331
+// ms against 592 ms at the 173 registers the compiler takes by itself (8 waves x
+// 4 groups, the survey of the file comment).
+template <int NW, int CWQ, int KS, int TS, bool TF, int WK, int TT = TT_DSR, bool PX = false, int S16 = 0>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(KS <= 8 ? 4 : 1)))
 void migrate_kernel(Params P) {
-    extern __shared__ float lds[];
-    migrate_tile<NW, CWQ, KS, TF, WK, true, TT, PX, S16>(P, blockIdx.z, blockIdx.x, blockIdx.y, lds);
+    extern __shared__ __align__(16) float lds[];
+    constexpr bool RREG = true;
+    migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16>(P, blockIdx.z, blockIdx.x, blockIdx.y, lds);
 }
 
 // Batched persistent form: work items (problem, bin, column tile, depth
@@ -812,23 +1045,23 @@ void migrate_kernel(Params P) {
 // tile field -1 - tile marks an item with no pair in aperture: zero store.
 // At least 4 wavefronts per SIMD (<= 128 VGPRs) for the 8-slot shapes, so
 // that two 8-wavefront workgroups share a CU as they do in single launches.
-template <int NW, int CWQ, int KS, bool TF, int WK, bool PX = false>
+template <int NW, int CWQ, int KS, int TS, bool TF, int WK, bool PX = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(KS <= 8 ? 4 : 2)))
 void migrate_batch_kernel(const Params* __restrict__ probs,
                                                                 const int4* __restrict__ items,
                                                                 int64_t n_items, unsigned int* counter) {
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ int64_t s_item;
     for (;;) {
-        __syncthreads();
+        __syncthreads();  // also: the last item's LDS is free
         if (threadIdx.x == 0) s_item = static_cast<int64_t>(atomicAdd(counter, 1u));
         __syncthreads();
         const int64_t it = s_item;
         if (it >= n_items) break;
         const int4 w = items[it];  // (problem, bin, tile, zchunk)
         const Params P = probs[w.x];
-        if (w.z < 0) zero_tile<NW, CWQ, KS>(P, w.y, -1 - w.z, w.w);
-        else migrate_tile<NW, CWQ, KS, TF, WK, false, TT_DSR, PX>(P, w.y, w.z, w.w, lds);
+        if (w.z < 0) zero_tile<NW, CWQ, KS, TS>(P, w.y, -1 - w.z, w.w);
+        else migrate_tile<NW, CWQ, KS, TS, TF, WK, false, TT_DSR, PX>(P, w.y, w.z, w.w, lds);
     }
 }
 
@@ -837,157 +1070,188 @@ void migrate_batch_kernel(const Params* __restrict__ probs,
 // ---------------------------------------------------------------------------
 
 // The plain kernels of one time precision (PX) for the weight and t_first cases.
-template <int NW, int CWQ, int KS, bool PX>
+template <int NW, int CWQ, int KS, int TS, bool PX>
 static hipError_t launch_migrate_dsr(const Params& P, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
     if (P.has_tf) {
         if (P.weight == W_COSCOS)
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_COSCOS, TT_DSR, PX>, grid, block, lds, s, P);
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_DSR, PX>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_COSCOS, TT_DSR, PX>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_DSR, PX>, grid, block, lds, s, P);
     }
     if (P.weight == W_COSCOS)
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_COSCOS, TT_DSR, PX>, grid, block, lds, s, P);
-    return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_DSR, PX>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_COSCOS, TT_DSR, PX>, grid, block, lds, s, P);
+    return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_DSR, PX>, grid, block, lds, s, P);
 }
 
 // The 16-bit staging kernels (float32 time), per storage type: square-root
 // times per weight and t_first case, the two table kinds per t_first case.
-template <int NW, int CWQ, int KS, int DT>
+template <int NW, int CWQ, int KS, int TS, int DT>
 static hipError_t launch_migrate_s16_dt(const Params& P, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
     if (P.ttab) {
         if (P.n_gx > 0) {
             if (P.has_tf)
-                return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_LTABLE, false, DT>, grid, block, lds, s, P);
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_LTABLE, false, DT>, grid, block, lds, s, P);
+                return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_LTABLE, false, DT>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_LTABLE, false, DT>, grid, block, lds, s, P);
         }
         if (P.has_tf)
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_TABLE, false, DT>, grid, block, lds, s, P);
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_TABLE, false, DT>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_TABLE, false, DT>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_TABLE, false, DT>, grid, block, lds, s, P);
     }
     if (P.has_tf) {
         if (P.weight == W_COSCOS)
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_COSCOS, TT_DSR, false, DT>, grid, block, lds, s, P);
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_DSR, false, DT>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_COSCOS, TT_DSR, false, DT>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_DSR, false, DT>, grid, block, lds, s, P);
     }
     if (P.weight == W_COSCOS)
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_COSCOS, TT_DSR, false, DT>, grid, block, lds, s, P);
-    return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_DSR, false, DT>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_COSCOS, TT_DSR, false, DT>, grid, block, lds, s, P);
+    return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_DSR, false, DT>, grid, block, lds, s, P);
 }
 
-template <int NW, int CWQ, int KS>
+template <int NW, int CWQ, int KS, int TS>
 static hipError_t launch_migrate_s16(const Params& P, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
-    if (P.dtype == BF16) return launch_migrate_s16_dt<NW, CWQ, KS, BF16>(P, grid, block, lds, s);
-    return launch_migrate_s16_dt<NW, CWQ, KS, F16>(P, grid, block, lds, s);
+    if (P.dtype == BF16) return launch_migrate_s16_dt<NW, CWQ, KS, TS, BF16>(P, grid, block, lds, s);
+    return launch_migrate_s16_dt<NW, CWQ, KS, TS, F16>(P, grid, block, lds, s);
 }
 
-template <int NW, int CWQ, int KS>
+template <int NW, int CWQ, int KS, int TS>
 static hipError_t launch_migrate_shape(const Params& P, hipStream_t s) {
     dim3 grid(P.n_coltiles, P.n_zchunks, P.n_bins), block(NW * 64);
     const size_t lds = lds_bytes(P, KS);
-    if (P.s16) return launch_migrate_s16<NW, CWQ, KS>(P, grid, block, lds, s);  // the host checked the kind
+    if (P.s16) return launch_migrate_s16<NW, CWQ, KS, TS>(P, grid, block, lds, s);  // the host checked the kind
     if (P.ttab && P.n_gx > 0) {  // laterally varying tables: W = 1
         if (P.prec) {
             if (P.has_tf)
-                return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_LTABLE, true>, grid, block, lds, s, P);
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_LTABLE, true>, grid, block, lds, s, P);
+                return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_LTABLE, true>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_LTABLE, true>, grid, block, lds, s, P);
         }
-        if (P.has_tf) return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_LTABLE>, grid, block, lds, s, P);
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_LTABLE>, grid, block, lds, s, P);
+        if (P.has_tf) return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_LTABLE>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_LTABLE>, grid, block, lds, s, P);
     }
     if (P.ttab) {  // table traveltimes: W = 1 (the host rejects other weights)
         if (P.prec) {
             if (P.has_tf)
-                return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_TABLE, true>, grid, block, lds, s, P);
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_TABLE, true>, grid, block, lds, s, P);
+                return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_TABLE, true>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_TABLE, true>, grid, block, lds, s, P);
         }
-        if (P.has_tf) return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_TABLE>, grid, block, lds, s, P);
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_TABLE>, grid, block, lds, s, P);
+        if (P.has_tf) return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_TABLE>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_TABLE>, grid, block, lds, s, P);
     }
     if (P.aa_max > 0) {  // anti-alias triangle filter
         if (P.has_tf) {
             if (P.weight == W_COSCOS)
-                return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_COSCOS, TT_AA>, grid, block, lds, s, P);
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, true, W_UNIT, TT_AA>, grid, block, lds, s, P);
+                return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_COSCOS, TT_AA>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, true, W_UNIT, TT_AA>, grid, block, lds, s, P);
         }
         if (P.weight == W_COSCOS)
-            return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_COSCOS, TT_AA>, grid, block, lds, s, P);
-        return launch_with_lds(migrate_kernel<NW, CWQ, KS, false, W_UNIT, TT_AA>, grid, block, lds, s, P);
+            return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_COSCOS, TT_AA>, grid, block, lds, s, P);
+        return launch_with_lds(migrate_kernel<NW, CWQ, KS, TS, false, W_UNIT, TT_AA>, grid, block, lds, s, P);
     }
-    if (P.prec) return launch_migrate_dsr<NW, CWQ, KS, true>(P, grid, block, lds, s);
-    return launch_migrate_dsr<NW, CWQ, KS, false>(P, grid, block, lds, s);
+    if (P.prec) return launch_migrate_dsr<NW, CWQ, KS, TS, true>(P, grid, block, lds, s);
+    return launch_migrate_dsr<NW, CWQ, KS, TS, false>(P, grid, block, lds, s);
 }
 
 // The batch kernel of (shape, t_first, weight, precision).
-template <int NW, int CWQ, int KS>
+template <int NW, int CWQ, int KS, int TS>
 static const void* batch_kernel_of(int has_tf, int weight, int prec) {
     if (prec) {
-        if (has_tf) return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, true, W_COSCOS, true>
-                                              : (const void*)migrate_batch_kernel<NW, CWQ, KS, true, W_UNIT, true>;
-        return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, false, W_COSCOS, true>
-                                  : (const void*)migrate_batch_kernel<NW, CWQ, KS, false, W_UNIT, true>;
+        if (has_tf) return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, true, W_COSCOS, true>
+                                              : (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, true, W_UNIT, true>;
+        return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, false, W_COSCOS, true>
+                                  : (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, false, W_UNIT, true>;
     }
-    if (has_tf) return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, true, W_COSCOS>
-                                          : (const void*)migrate_batch_kernel<NW, CWQ, KS, true, W_UNIT>;
-    return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, false, W_COSCOS>
-                              : (const void*)migrate_batch_kernel<NW, CWQ, KS, false, W_UNIT>;
+    if (has_tf) return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, true, W_COSCOS>
+                                          : (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, true, W_UNIT>;
+    return weight == W_COSCOS ? (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, false, W_COSCOS>
+                              : (const void*)migrate_batch_kernel<NW, CWQ, KS, TS, false, W_UNIT>;
 }
 
-template <int NW, int CWQ, int KS>
+template <int NW, int CWQ, int KS, int TS>
 static hipError_t launch_migrate_batch_shape(const Params* probs, const int4* items, int64_t n_items,
                                              unsigned int* counter, int has_tf, int weight, int prec, int n_wg,
                                              size_t lds, hipStream_t s) {
     dim3 grid(n_wg), block(NW * 64);
     using K = void (*)(const Params*, const int4*, int64_t, unsigned int*);
-    const K kern = reinterpret_cast<K>(const_cast<void*>(batch_kernel_of<NW, CWQ, KS>(has_tf, weight, prec)));
+    const K kern = reinterpret_cast<K>(const_cast<void*>(batch_kernel_of<NW, CWQ, KS, TS>(has_tf, weight, prec)));
     return launch_with_lds(kern, grid, block, lds, s, probs, items, n_items, counter);
 }
 
-// (waves, column groups per wave, depth slots, LDS budget for the trace block)
-#define KM_MIGRATE_SHAPES(X) \
-    X(4, 4, 8, 32768)        \
-    X(16, 4, 8, 155648)      \
-    X(8, 4, 8, 77824)        \
-    X(4, 3, 16, 49152)       \
-    X(4, 2, 16, 49152)
-
-static const TileShape kMigrateShapes[] = {
-#define X(nw, cwq, ks, lb) {nw, cwq, ks, lb},
-    KM_MIGRATE_SHAPES(X)
-#undef X
+// Waves, column groups per wave, depth slots, LDS budget for the trace block,
+// trace parts.  The small tiles (ms, square-root times, before: 8 waves x 4 groups):
+//   1536 traces -> 8 x 128 x 200 points    0.521 -> 0.065  (16 waves, 4 parts, 4 slots)
+//   6144 traces -> 8 x 256 x 256           1.91  -> 0.289  (16 waves, 4 parts, 8 slots)
+//   16384 traces -> 16 x 512 x 400         2.57  -> 1.89   (4 waves, 1 group)
+//   20736 traces -> 10 x 80 x 80 x 300     17.9  -> 14.6   (8 waves, 2 groups)
+// build.py compiles this file once per shape (KM_PART = its index: a shape has
+// about 50 kernels) and once without KM_PART for the dispatch.
+constexpr TileShape kMigrateShapes[] = {
+    {4, 4, 8, 32768, 0, 1},
+    {16, 4, 8, 155648, 0, 1},
+    {8, 4, 8, 77824, 0, 1},
+    {4, 3, 16, 49152, 0, 1},
+    {4, 2, 16, 49152, 0, 1},
+    {8, 2, 8, 77824, 0, 1},
+    {4, 1, 8, 40960, 0, 1},
+    {16, 1, 8, 77824, 0, 4},
+    {16, 1, 4, 77824, 0, 4},
 };
+constexpr int kMigrateShapeCount = static_cast<int>(sizeof(kMigrateShapes) / sizeof(kMigrateShapes[0]));
 
-int migrate_shape_count() { return static_cast<int>(sizeof(kMigrateShapes) / sizeof(kMigrateShapes[0])); }
+using MigrateLaunch = hipError_t (*)(const Params& P, hipStream_t s);
+using MigrateBatchLaunch = hipError_t (*)(const Params* probs, const int4* items, int64_t n_items,
+                                          unsigned int* counter, int has_tf, int weight, int prec, int n_wg,
+                                          size_t lds, hipStream_t s);
+using MigrateBatchKernel = const void* (*)(int has_tf, int weight, int prec);
+struct MigratePart {
+    MigrateLaunch launch;
+    MigrateBatchLaunch launch_batch;
+    MigrateBatchKernel batch_kernel;
+};
+template <int SHAPE>
+MigratePart migrate_part();
+
+#ifdef KM_PART
+
+template <>
+MigratePart migrate_part<KM_PART>() {
+    constexpr TileShape S = kMigrateShapes[KM_PART];
+    return {launch_migrate_shape<S.waves, S.column_groups, S.depth_slots, S.trace_parts>,
+            launch_migrate_batch_shape<S.waves, S.column_groups, S.depth_slots, S.trace_parts>,
+            batch_kernel_of<S.waves, S.column_groups, S.depth_slots, S.trace_parts>};
+}
+
+#else
+
+template <int... I>
+static MigratePart part_of(int shape, std::integer_sequence<int, I...>) {
+    MigratePart p{nullptr, nullptr, nullptr};
+    ((shape == I ? (void)(p = migrate_part<I>()) : (void)0), ...);
+    return p;
+}
+
+static MigratePart part_of(int shape) {
+    return part_of(shape, std::make_integer_sequence<int, kMigrateShapeCount>());
+}
+
+int migrate_shape_count() { return kMigrateShapeCount; }
 const TileShape& migrate_shape(int i) { return kMigrateShapes[i]; }
 
 hipError_t launch_migrate(int shape, const Params& P, hipStream_t s) {
-    int i = 0;
-#define X(nw, cwq, ks, lb) \
-    if (shape == i) return launch_migrate_shape<nw, cwq, ks>(P, s); \
-    ++i;
-    KM_MIGRATE_SHAPES(X)
-#undef X
-    return hipErrorInvalidValue;
+    const MigratePart p = part_of(shape);
+    return p.launch ? p.launch(P, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_migrate_batch(int shape, const Params* probs, const int4* items, int64_t n_items,
                                 unsigned int* counter, int has_tf, int weight, int prec, int n_wg, size_t lds,
                                 hipStream_t s) {
-    int i = 0;
-#define X(nw, cwq, ks, lb) \
-    if (shape == i) return launch_migrate_batch_shape<nw, cwq, ks>(probs, items, n_items, counter, has_tf, weight, prec, n_wg, lds, s); \
-    ++i;
-    KM_MIGRATE_SHAPES(X)
-#undef X
-    return hipErrorInvalidValue;
+    const MigratePart p = part_of(shape);
+    return p.launch_batch ? p.launch_batch(probs, items, n_items, counter, has_tf, weight, prec, n_wg, lds, s)
+                          : hipErrorInvalidValue;
 }
 
 const void* migrate_batch_kernel_ptr(int shape, int has_tf, int weight, int prec) {
-    int i = 0;
-#define X(nw, cwq, ks, lb) \
-    if (shape == i) return batch_kernel_of<nw, cwq, ks>(has_tf, weight, prec); \
-    ++i;
-    KM_MIGRATE_SHAPES(X)
-#undef X
-    return nullptr;
+    const MigratePart p = part_of(shape);
+    return p.batch_kernel ? p.batch_kernel(has_tf, weight, prec) : nullptr;
 }
+
+#endif
 
 }  // namespace km

@@ -8,24 +8,25 @@ namespace km {
 // ---------------------------------------------------------------------------
 // Pair counts.  Same lane layout as migration (4 column groups x 16 depths per
 // wavefront slot); the aperture decision is the kernels' float32 one.
-// Grid (column tiles, depth chunks, bins); tile = cpt columns, chunk = 16 ks
+// Grid (column tiles, depth chunks, bins); tile = cpt columns, chunk = zspan
 // depths.  counts (optional) gets the totals, costs (optional) one in-aperture
 // count per workgroup at ((bin * n_zchunks + zchunk) * n_coltiles + tile).
 // ---------------------------------------------------------------------------
 constexpr int kCountWaves = 4;
 
-__global__ __launch_bounds__(kCountWaves * 64) void count_kernel(Params P, int cpt, int ks,
+__global__ __launch_bounds__(kCountWaves * 64) void count_kernel(Params P, int cpt, int zspan,
                                                                  unsigned long long* counts,
                                                                  unsigned long long* costs) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x / 64;
     const int g = lane / kGroup, d = lane % kGroup;
     const int b = blockIdx.z, zc = blockIdx.y, tile = blockIdx.x;
     const int ncol = P.nx * P.ny;
-    const int z0 = chunk_z0<false>(P.nz, zc, gridDim.y, ks * kGroup);
+    const int z0 = zc * zspan;
+    const int z1 = min(z0 + zspan, P.nz);
     const int64_t lo = lower_bound_bin(P.bin, P.n_traces, b);
     const int64_t hi = lower_bound_bin(P.bin, P.n_traces, b + 1);
     const float tfu = P.has_tf ? static_cast<float>(kLead) - P.tf_off : 0.0f;  // t_first / dt
-    constexpr int kMaxSlots = 16;  // host guarantees ks <= kMaxSlots
+    constexpr int kMaxSlots = 16;  // host guarantees zspan <= 16 kMaxSlots
     float Rk[kMaxSlots], Ak[kMaxSlots], Bk[kMaxSlots];
     float rmax = -1.0f;
 #pragma unroll
@@ -34,7 +35,7 @@ __global__ __launch_bounds__(kCountWaves * 64) void count_kernel(Params P, int c
         Rk[k] = -1.0f;
         Ak[k] = 1.0f;
         Bk[k] = 0.0f;
-        if (k < ks && iz >= 0 && iz < P.nz) {
+        if (iz < z1) {
             Rk[k] = P.r2[iz];
             Ak[k] = static_cast<float>(static_cast<double>(P.t0sq[iz]) * P.inv_dt2);
             Bk[k] = static_cast<float>(static_cast<double>(P.s2[iz]) * P.inv_dt2);
@@ -95,19 +96,19 @@ __global__ void zero_u64_kernel(unsigned long long* p, int n) {
 
 hipError_t launch_count(const Params& P, unsigned long long* counts, hipStream_t s) {
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, counts, 2);
-    const int cpt = 64, ks = 16;
+    const int cpt = 64, zspan = 256;
     const int ncol = P.nx * P.ny;
-    dim3 grid((ncol + cpt - 1) / cpt, (P.nz + ks * kGroup - 1) / (ks * kGroup), P.n_bins);
+    dim3 grid((ncol + cpt - 1) / cpt, (P.nz + zspan - 1) / zspan, P.n_bins);
     if (grid.x && grid.y && grid.z)
-        hipLaunchKernelGGL(count_kernel, grid, dim3(kCountWaves * 64), 0, s, P, cpt, ks, counts, nullptr);
+        hipLaunchKernelGGL(count_kernel, grid, dim3(kCountWaves * 64), 0, s, P, cpt, zspan, counts, nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_item_costs(const Params& P, int shape_ks, int cols_per_tile, unsigned long long* costs,
+hipError_t launch_item_costs(const Params& P, int cols_per_tile, unsigned long long* costs,
                              hipStream_t s) {
     dim3 grid(P.n_coltiles, P.n_zchunks, P.n_bins);
     if (grid.x && grid.y && grid.z)
-        hipLaunchKernelGGL(count_kernel, grid, dim3(kCountWaves * 64), 0, s, P, cols_per_tile, shape_ks, nullptr,
+        hipLaunchKernelGGL(count_kernel, grid, dim3(kCountWaves * 64), 0, s, P, cols_per_tile, P.zspan, nullptr,
                            costs);
     return hipGetLastError();
 }

@@ -7,6 +7,7 @@ FP64 oracle or float64.
 Migration's tolerance is the parity bar of band-limited traces, 1e-5 relative
 L2; the filter's 1e-6 of sum |h| max |x| (65 float32 roundings at most); the dot
 product is a float64 sum of exact products, 1e-12 of the sum of magnitudes."""
+import dataclasses
 
 import numpy as np
 import pytest
@@ -25,6 +26,62 @@ def ops():
 
     _lib.load()
     return ops
+
+
+def rel_l2(a, b):
+    return float(np.linalg.norm(a.astype(np.float64) - b) / max(np.linalg.norm(b), 1e-300))
+
+
+def shot_order(p, run):
+    """The problem with its traces in runs of `run` that share a source (bins kept)."""
+    src = p.src.copy()
+    for j in range(p.n_traces):
+        src[j] = src[j - j % run]
+    return dataclasses.replace(p, src=src)
+
+
+# traces, samples, nx, ny, nz, bins, run of equal sources, t_first, weight
+CASES = [
+    (1, 200, 1, 1, 1, 1, 1, 0.0, survey.WEIGHT_COSCOS),        # a single pair
+    (63, 300, 5, 1, 15, 2, 3, 0.0, survey.WEIGHT_UNIT),        # one partial slot, a partial wavefront of bins
+    (65, 300, 17, 3, 33, 3, 16, 0.1, survey.WEIGHT_COSCOS),    # one column, one depth past a tile
+    (1100, 250, 4, 4, 140, 1, 17, 0.0, survey.WEIGHT_COSCOS),  # more near traces than the list holds
+    (4097, 64, 16, 1, 32, 70, 2, 0.0, survey.WEIGHT_COSCOS),   # the bin search's second step, empty bins
+    (300, 1500, 33, 2, 257, 1, 300, 0.0, survey.WEIGHT_COSCOS),  # windows longer than one staging step
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("prec", ["fp32", "extended"])
+def test_migrate_edges(ops, oracle_lib, case, prec):
+    n, n_t, nx, ny, nz, bins, run, t_first, weight = case
+    p = shot_order(survey.make_random(n + nz, n, n_t, nx, ny, nz, bins, t_first=t_first, weight=weight), run)
+    dp = ops.to_device(p, prec=prec)
+    ref = oracle_lib.migrate(p)
+    first = None
+    for tile in [-1] + list(range(ops.tile_count(0))):
+        img = ops.migrate(dp, tile=tile)
+        if not np.any(ref):
+            assert not torch.any(img), tile
+            continue
+        assert rel_l2(img.cpu().numpy(), ref) <= 1e-5, (tile, prec)
+        if 0 <= tile < 7:  # tiles without trace parts add a point's pairs in trace order: the same bits
+            first = img if first is None else first
+            assert torch.equal(img, first), tile
+
+
+def test_table_pairs_at_the_aperture_edge(ops, oracle_lib):
+    # amplitude tables and depth slots that only some columns of a group reach:
+    # every tile without trace parts gives the same bits, all within 1e-5
+    p = survey.make_random(11, 120, 400, 29, 5, 150, 3, aperture_deg=35.0)
+    p = survey.with_curved_ray_table(shot_order(p, 6), 10.0, amplitude=True)
+    ref = oracle_lib.migrate(p)
+    dp = ops.to_device(p)
+    a = ops.migrate(dp, tile=0)
+    for tile in range(ops.tile_count(0)):
+        img = ops.migrate(dp, tile=tile)
+        assert rel_l2(img.cpu().numpy(), ref) <= 1e-5, tile
+        assert tile >= 7 or torch.equal(img, a), tile
 
 
 # bins, ny, nx, nz, lags, window
