@@ -22,7 +22,7 @@ LIB = os.path.join(HERE, "libkirchhoff.so")
 SOURCES = ["km_api.cpp", "km_count.cpp", "km_migrate.hip", "km_demigrate.hip", "km_misc.hip", "km_cig.hip",
            "km_filter.hip"]
 # sources compiled once more per tile shape (-DKM_PART=i), so that the shapes compile in parallel
-PARTS = {"km_migrate.hip": 9}
+PARTS = {"km_migrate.hip": 9, "km_demigrate.hip": 6}
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
