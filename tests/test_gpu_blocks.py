@@ -131,3 +131,21 @@ def test_filter_infinity_stays_within_its_taps(ops):
     h = torch.ones(5, device="cuda")
     y = ops.trace_filter(x, h, 2)[0].cpu().numpy()
     assert np.isinf(y[98:103]).all() and (y[:98] == 0).all() and (y[103:] == 0).all()
+
+
+@pytest.mark.parametrize("n", [0, 1, 3, 4, 5, 1023, 4 * 4 * 256 * 3 + 7, 1 << 21])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_streams(ops, n, shift):
+    g = torch.Generator(device="cuda").manual_seed(n + shift)
+    a = torch.randn(n + shift, generator=g, device="cuda")[shift:]
+    b = torch.randn(n + shift, generator=g, device="cuda")[shift:]
+    ref = float((a.double() * b.double()).sum())
+    size = float((a.double() * b.double()).abs().sum())
+    assert abs(float(ops.dot_f64(a, b)) - ref) <= 1e-12 * size
+    y = b.clone()[:] if shift == 0 else torch.cat([b[:1], b])[1:]
+    ops.axpby(2.5, a, -0.5, y)
+    ref_y = torch.addcmul(-0.5 * b, a, torch.full_like(a, 2.5))
+    assert n == 0 or float((y - ref_y).abs().max()) <= 2.0 ** -22 * 10.0
+    y.fill_(float("nan"))
+    ops.axpby(3.0, a, 0.0, y)
+    assert torch.equal(y, 3.0 * a)
