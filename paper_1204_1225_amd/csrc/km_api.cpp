@@ -168,7 +168,7 @@ bool migrate_block_params(km::Params& P, int budget, int ks, int waves) {
     // as many bytes), anti-aliasing float64 running sums over nt + 4 max_half
     // + 9 positions
     const int64_t nt = P.nt;
-    const int64_t need = (P.aa_max > 0 ? 2 * (nt + 4 * P.aa_max + 9)
+    const int64_t need = (P.aa_max > 0 ? 2 * ((nt + 4 * P.aa_max + 9 + 3) & ~int64_t{3})
                           : P.ttab   ? (P.s16 ? (nt + 4) / 2 : nt + 3)
                                      : (P.s16 ? nt + 2 : 2 * ((nt + 5) & ~int64_t{3}))) + 3 & ~int64_t{3};
     // the list of near traces holds two passes of its filter, less beside the longest records

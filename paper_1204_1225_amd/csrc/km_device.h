@@ -745,6 +745,28 @@ __device__ __forceinline__ int wave_scan(int v) {
     return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
 }
 
+// The same for float64 (two halves per step), the value of the lane before (0
+// for lane 0: 0x138 shifts the wavefront by one) and of the last lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_d(double v) {
+    constexpr bool kZero = ROWS == 0xf;  // lanes without a source read 0
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, kZero),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, kZero));
+}
+__device__ __forceinline__ double wave_scan_d(double v) {
+    v += dpp_d<0x111, 0xf>(v);
+    v += dpp_d<0x112, 0xf>(v);
+    v += dpp_d<0x114, 0xf>(v);
+    v += dpp_d<0x118, 0xf>(v);
+    v += dpp_d<0x142, 0xa>(v);
+    return v + dpp_d<0x143, 0xc>(v);
+}
+__device__ __forceinline__ double prev_lane_d(double v) { return dpp_d<0x138, 0xf>(v); }
+__device__ __forceinline__ double last_lane_d(double v) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), kLanes - 1),
+                            __builtin_amdgcn_readlane(__double2loint(v), kLanes - 1));
+}
+
 // Wavefront minimum / maximum (every lane gets it, as a uniform value).
 __device__ __forceinline__ float wave_min(float v) { return uniform_f(rows_min(group_min(v))); }
 __device__ __forceinline__ float wave_max(float v) { return uniform_f(rows_max(group_max(v))); }

@@ -149,3 +149,16 @@ def test_streams(ops, n, shift):
     y.fill_(float("nan"))
     ops.axpby(3.0, a, 0.0, y)
     assert torch.equal(y, 3.0 * a)
+
+
+# windows of one position up to several staging steps of 256, 16-bit rows at odd samples
+@pytest.mark.parametrize("n_t,dtype", [(1, "f32"), (3, "f32"), (254, "bf16"), (257, "f16"), (1031, "f32"), (1500, "bf16")])
+def test_anti_alias_windows(ops, oracle_lib, n_t, dtype):
+    p = survey.make_random(n_t, 70, n_t, 19, 3, 70, 2, weight=survey.WEIGHT_UNIT)
+    p = dataclasses.replace(p, aa=(12.0, 12.0, 16))
+    dp = ops.to_device(p, dtype=dtype)
+    if dtype != "f32":
+        p = dataclasses.replace(p, data=survey.quantise(p.data, dtype)[2])
+    ref = oracle_lib.migrate(p)
+    for tile in [-1] + list(range(ops.tile_count(0))):
+        assert rel_l2(ops.migrate(dp, tile=tile).cpu().numpy(), ref) <= 1e-5, tile
