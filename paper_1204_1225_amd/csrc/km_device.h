@@ -794,6 +794,34 @@ __device__ __forceinline__ int slot_depth(int z0, int k, int d) {
     return z0 + (k >> 1) * (2 * kGroup) + 2 * d + (k & 1);
 }
 
+// End of the record (in the unit of the tables' square roots, past the last
+// time that touches a sample) and the largest offset of some traces.
+struct RecordEnd {
+    float end, offset;
+};
+
+// Square of the longest leg with which those traces' times t = sqrt(A + B hs^2) +
+// sqrt(A + B hr^2) can still end within the record; negative when none can, infinite
+// (or NaN) when there is no bound.  With h the longer leg, the other is at
+// least max(h - offset, 0), so t >= f(h) = sqrt(A + B h^2) + sqrt(A + B max(h -
+// offset, 0)^2), and f(h) = end is solved for h: in closed form up to h = offset,
+// beyond it on the ellipse through both ends, x = h - offset / 2 with
+// B x^2 (1 - B offset^2 / end^2) = end^2 / 4 - A - B offset^2 / 4.
+// 1.001 covers the roundings here and of the legs; 1 - B offset^2 / end^2 below 0.02
+// would magnify them, so there no bound is given.
+__device__ __forceinline__ float record_aperture(float A, float B, RecordEnd E) {
+    const float T = E.end, o = E.offset, s = __builtin_amdgcn_sqrtf(A);
+    if (!(B > 0.0f)) return __builtin_inff();
+    if (T <= 2.0f * s) return -1.0f;
+    const float ib = __builtin_amdgcn_rcpf(B), o2 = o * o;
+    const float one = T * (T - 2.0f * s) * ib;  // the other leg 0
+    const float v = 1.0f - B * o2 * __builtin_amdgcn_rcpf(T * T);
+    const float x2 = (0.25f * (T * T - B * o2) - A) * ib * __builtin_amdgcn_rcpf(v);
+    const float x = __builtin_amdgcn_sqrtf(fmaxf(x2, 0.0f)) + 0.5f * o;
+    const float two = v > 0.02f ? fmaxf(x * x, o2) : __builtin_inff();
+    return 1.001f * (one > o2 ? two : one);
+}
+
 // Per-depth tables of one depth chunk.  Lane d of every group holds depth
 // slot_depth(z0, k, d) in slot k.  A lane is valid if its depth exists in the
 // chunk (0 <= iz < z1) and (for
@@ -815,9 +843,10 @@ struct ChunkTables {
     uint32_t clean;  // bit k: every lane of slot k is valid (wavefront-uniform)
 };
 
-template <int KS, int IL = 1, int TT = TT_DSR, bool PX = false>
+// E (given with CUT): no aperture value beyond record_aperture's.
+template <int KS, int IL = 1, int TT = TT_DSR, bool PX = false, bool CUT = false>
 __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int z1, int d, bool zero_weight_guard,
-                                                  ChunkTables<KS>& T, float* sR) {
+                                                  ChunkTables<KS>& T, float* sR, RecordEnd E = RecordEnd{}) {
     const int lane = threadIdx.x & (kLanes - 1);
     float rmax = -1.0f;
     float rlo_mine = __builtin_inff(), rhi_mine = -__builtin_inff();
@@ -825,30 +854,26 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int z
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
         const int iz = slot_depth<IL>(z0, k, d);
-        // invalid lanes: a = 1 for every leg (finite time and weight), never inside
-        float A = 1.0f, B = 0.0f, R = -1.0f;
-        bool valid = false;
-        if (iz >= 0 && iz < z1) {
-            if (is_table(TT)) {
-                // table times carry no t0sq / s2; A, B are unused and W = 1
-                valid = true;
-                A = 0.0f;
-                R = P.r2[iz];
-            } else {
-                const float t0 = P.t0sq[iz];
-                valid = !(zero_weight_guard && !(t0 > 0.0f));
-                if (valid) {
-                    if (PX) {
-                        A = t0 == 0.0f ? kTinyA : t0;
-                        B = P.s2[iz];
-                    } else {
-                        A = static_cast<float>(static_cast<double>(t0) * P.inv_dt2);
-                        B = static_cast<float>(static_cast<double>(P.s2[iz]) * P.inv_dt2);
-                    }
-                    R = P.r2[iz];
-                }
-            }
+        // invalid lanes: a = 1 for every leg (finite time and weight), never inside.
+        // Every lane loads (from a depth that exists), so that the loads of all slots
+        // are in flight together; behind a branch each slot waited twice.
+        const bool in = iz >= 0 && iz < z1;
+        const int zl = max(min(iz, z1 - 1), 0);
+        const float r2 = P.r2[zl];
+        float A = 1.0f, B = 0.0f;
+        bool valid = in;
+        if (is_table(TT)) {
+            if (in) A = 0.0f;  // table times carry no t0sq / s2; A, B are unused and W = 1
+        } else {
+            const float t0 = P.t0sq[zl], s2 = P.s2[zl];
+            valid = in && !(zero_weight_guard && !(t0 > 0.0f));
+            const float a = PX ? (t0 == 0.0f ? kTinyA : t0) : static_cast<float>(static_cast<double>(t0) * P.inv_dt2);
+            const float b = PX ? s2 : static_cast<float>(static_cast<double>(s2) * P.inv_dt2);
+            A = valid ? a : A;
+            B = valid ? b : B;
         }
+        float R = valid ? r2 : -1.0f;
+        if (CUT) R = fminf(R, record_aperture(A, B, E));
         T.A[k] = A;
         T.B[k] = B;
         T.R[k] = R;

@@ -162,3 +162,29 @@ def test_anti_alias_windows(ops, oracle_lib, n_t, dtype):
     ref = oracle_lib.migrate(p)
     for tile in [-1] + list(range(ops.tile_count(0))):
         assert rel_l2(ops.migrate(dp, tile=tile).cpu().numpy(), ref) <= 1e-5, tile
+
+
+# A record that most pairs outlast holds the first samples of a longer one: the same
+# taps in another order, so each sample within two roundings (and the anti-alias
+# kernel's double suffix sums, float64, within 1e-9 of the long record's largest).
+@pytest.mark.parametrize("n_t,t_first,weight", [(1, 0.0, survey.WEIGHT_UNIT), (60, 0.0, survey.WEIGHT_COSCOS),
+                                                (130, 0.35, survey.WEIGHT_COSCOS), (64, 0.5, survey.WEIGHT_UNIT)])
+@pytest.mark.parametrize("kind", ["fp32", "extended", "aa", "table", "ltable"])
+@pytest.mark.parametrize("spread", [40.0, 900.0])
+def test_adjoint_pairs_past_the_record(ops, n_t, t_first, weight, kind, spread):
+    p = survey.make_random(n_t + int(spread), 45, n_t, 37, 6, 140, 2, t_first=t_first, weight=weight, spread=spread)
+    if kind == "aa":
+        p = dataclasses.replace(p, aa=(12.0, 12.0, 8))
+    elif kind == "table":
+        p = survey.with_curved_ray_table(p, 10.0, amplitude=True)
+    elif kind == "ltable":
+        p = survey.with_lateral_tables(p, lambda x, y: 1500.0 + 0.05 * x, 0.5, -300.0, 800.0, 700.0, 700.0, 4, 4, dh=20.0)
+    prec = "extended" if kind == "extended" else "fp32"
+    m = torch.from_numpy(survey.random_image(p, n_t)).cuda()
+    long = ops.to_device(dataclasses.replace(p, n_t=n_t + 900, data=None), prec=prec)
+    ref = ops.demigrate(long, m, tile=0).cpu().numpy().astype(np.float64)
+    largest, ref = np.abs(ref).max(), ref[:, :n_t]
+    dp = ops.to_device(p, prec=prec)
+    for tile in [-1] + list(range(ops.tile_count(1))):
+        d = ops.demigrate(dp, m, tile=tile).cpu().numpy()
+        assert np.all(np.abs(d - ref) <= 2.0 ** -22 * np.abs(ref) + 1e-9 * largest), tile
