@@ -390,30 +390,42 @@ int64_t migrate_workgroups(int shape, const km_grid& g) {
 // function of the shape, summed over a batch's problems).  A large tile stages
 // and examines a trace once for many columns; a small image needs small tiles
 // to fill 256 CUs, and the smallest ones several wavefronts on the same columns
-// with the traces dealt out among them (trace_parts).  Each line is where the two
-// sides ran alike: 3000 workgroups of tile 5 ran 14.6 ms against 14.8 ms with
-// tile 6, 576 of them 1.97 against 1.64 ms; 512 of tile 6 ran 0.064 ms against
-// 0.074 ms with tile 7, 256 of them 0.61 against 0.29 ms; 256 of tile 7 ran 0.29
-// ms against 0.38 ms with tile 8, 128 of them 0.090 against 0.065 ms.
+// with the traces dealt out among them (trace_parts; one workgroup per CU is
+// enough for those, so they take level 3: twice the LDS, larger blocks).  Each
+// line is where the two sides ran alike.  Square-root times: 3000 workgroups of
+// tile 5 ran 14.6 ms against 14.8 ms with tile 6, 576 of them 1.97 against 1.64
+// ms; 512 of tile 6 ran 0.064 ms against 0.074 ms with tile 7, 256 of them 0.61
+// against 0.29 ms; 256 of tile 7 ran 0.29 ms against 0.38 ms with tile 8, 128 of
+// them 0.090 against 0.065 ms.  Tables and the anti-alias filter stage more per
+// trace, so tile 6 (16 columns) never pays: 512 workgroups of tile 5 ran 4.37 ms
+// against 6.6 ms with tile 6 and 5.4 ms with tile 7 (table), 8.1 against 11.4
+// and 9.1 ms (anti-alias); 480 of them 6.9 ms against 5.5 ms with tile 7
+// (lateral tables).
 // Tile 2 (128 columns) where the grid of tile 5 would pass 2^32 threads.
 template <typename Workgroups>
 int default_migrate_tile(int kind, Workgroups workgroups) {
-    if (workgroups(5) >= int64_t{1} << 22) return 2;
-    if (workgroups(5) >= 1024) return 5;  // 64 columns x 128 depths
-    const int64_t n = workgroups(6);      // 16 columns x 128 depths, also of shape 7
-    if (n >= 400) return 6;
-    return n >= 192 ? 7 : 8;              // 4 parts on 16 columns x 128 or 64 depths
+    const int64_t wide = workgroups(5);  // 64 columns x 128 depths
+    if (wide >= int64_t{1} << 22) return 2;
+    if (wide >= (kind == KIND_DSR ? 1024 : 512)) return 5;
+    const int64_t n = workgroups(6);     // 16 columns x 128 depths, also of shape 7
+    if (kind == KIND_DSR && n >= 400) return 6;
+    return (n >= 192 ? 7 : 8) + 3 * kTileLevelStride;  // 4 parts on 16 columns x 128 or 64 depths
 }
 
-// Untuned choice for the adjoint: 8 waves x 4 slots x 1 trace quad (16 waves
-// where there are no more quads than CUs: 0.117 ms against 0.151 ms on 225 quads),
-// and 16 waves x 8 slots x 3 quads with table traveltimes, whose table gathers
-// favour more traces per workgroup; 8 waves x 8 slots x 3 quads with laterally
-// varying tables (16 reads per pair).
-int default_demigrate_tile(int kind, int64_t n_traces) {
-    if (kind == KIND_LTABLE) return 4;
-    if (kind == KIND_TABLE) return 1;
-    return n_traces <= 4 * 256 ? 5 : 3;
+// Untuned choice for the adjoint: 8 waves x 4 slots x 1 trace quad, with 16
+// waves where there are no more quads than CUs (0.117 ms against 0.151 ms on 225
+// quads).  With table traveltimes 16 waves x 8 slots x 3 quads, and 8 waves x 8
+// slots x 3 quads with laterally varying tables: their gathers favour more traces
+// per workgroup (350 ms against 369 ms and 223 ms against 227 ms on 50 000
+// traces), once those workgroups fill the chip.  Below, fewer quads: 31.0 ms
+// against 32.4 ms with 2 on 18 000 traces (table), 0.20 ms against 0.25 ms with 1 on
+// 1800; lateral 6.9 ms against 8.4 ms with 1 on 8000, extended times
+// 1.8 ms against 5.0 ms on 4096.
+int default_demigrate_tile(int kind, int prec, int64_t n_traces) {
+    if (n_traces <= 4 * 256) return 5;
+    if (kind == KIND_LTABLE) return n_traces >= 12 * 2048 ? 4 : prec == KM_TIME_EXTENDED ? 0 : 3;
+    if (kind == KIND_TABLE) return n_traces >= 12 * 1536 ? 1 : n_traces >= 12 * 256 ? 2 : 3;
+    return 3;
 }
 
 // Whether a tile can run problems of a class: a tile of op, and a 16-bit
@@ -561,7 +573,7 @@ km_status demigrate_impl(const float* image, const km_grid* grid, const km_trave
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
     st = pick_tile(1, tile, out->dtype, kind, tt->time_precision, grid->nz, out->n_samples,
-                   [&] { return default_demigrate_tile(kind, out->n_traces); }, &shape);
+                   [&] { return default_demigrate_tile(kind, tt->time_precision, out->n_traces); }, &shape);
     if (st != KM_OK) return st;
     return run_op(1, out, grid, tt, weight, const_cast<float*>(image), accumulate, shape, s, tab, aa, lat);
 }
@@ -1025,7 +1037,7 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
     km_status st = pick_tile(0, tile, probs[0].traces.dtype, KIND_DSR, probs[0].tt.time_precision, max_nz, max_nt,
                              [&] {
                                  const int t = default_migrate_tile(KIND_DSR, workgroups);
-                                 return workgroups(t) > max_items ? 2 : t;
+                                 return workgroups(t % kTileLevelStride) > max_items ? 2 : t;
                              },
                              &B.tile);
     if (st != KM_OK) return st;
