@@ -146,6 +146,15 @@ km::Params base_params(const km_traces* t, const km_grid* g, const km_traveltime
     return P;
 }
 
+// Samples of an LDS row: the record between zeros, with the anti-alias filter also
+// the reach of its triangles.
+int row_samples(int64_t n_samples, const km_antialias* aa) {
+    const int64_t ends = aa && aa->max_half > 0 ? 2 * (2 * aa->max_half + 5) : km::kLead + kTailPad;
+    return static_cast<int>((n_samples + ends + 3) / 4 * 4);
+}
+// LDS bytes of four of the adjoint's float64 rows.
+int64_t quad_row_bytes(int64_t n_samples, const km_antialias* aa) { return int64_t{32} * row_samples(n_samples, aa); }
+
 // Traces per LDS block for a shape's budget; 0 if even one row does not fit.
 int traces_per_block(int lt, int budget, int ks, int row_bytes_per_sample) {
     const int64_t fixed = static_cast<int64_t>(16) * ks * 4 + (ks > 0 ? km::kBoxFloats * 4 : 0);
@@ -236,7 +245,12 @@ km_status shape_params(int op, int tile, km::Params& P) {
         // whole quads of traces keep every group busy
         // (anti-aliased rows are longer: the budget grows with them, keeping whole quads)
         const int extra = P.aa_max > 0 ? 4 * 8 * (P.lt - (P.nt + km::kLead + kTailPad + 3) / 4 * 4) : 0;
-        P.tb = traces_per_block(P.lt, S.lds_budget + extra, 0, 8);
+        // Records longer than the budget's take a whole quad too, as long as it fits beside
+        // the kernel's small tables: with 2 or 3 traces per workgroup half or a quarter
+        // of its lanes had no work (6000 traces of 2400 samples: 0.66 ms, now 0.45 ms).
+        const int64_t quad = int64_t{4} * (8 * static_cast<int64_t>(P.lt) + 16);
+        const int64_t budget = S.lds_budget + extra;
+        P.tb = traces_per_block(P.lt, static_cast<int>(std::max(budget, quad + 256 <= kMaxLds ? quad : 0)), 0, 8);
         if (S.max_quads > 0) P.tb = std::min(P.tb, 4 * S.max_quads);
         if (level > 0) P.tb = std::min(P.tb, 4 * level);
         if (P.tb >= 4) P.tb &= ~3;
@@ -421,11 +435,18 @@ int default_migrate_tile(int kind, Workgroups workgroups) {
 // against 32.4 ms with 2 on 18 000 traces (table), 0.20 ms against 0.25 ms with 1 on
 // 1800; lateral 6.9 ms against 8.4 ms with 1 on 8000, extended times
 // 1.8 ms against 5.0 ms on 4096.
-int default_demigrate_tile(int kind, int prec, int64_t n_traces) {
+// Records whose quad of float64 rows lets only two workgroups share a CU take 8
+// slots (0.43 ms against 0.45 ms on 2400 samples; three workgroups of 1600
+// samples 0.40 ms with 4 slots against 0.42 ms), and where one fills it, 16 waves (0.49
+// ms against 0.65 ms on 3000 samples; extended times, 4 slots: 0.69 ms against 0.77 ms).
+int default_demigrate_tile(int kind, int prec, int64_t n_traces, int64_t quad_bytes) {
+    const bool fp32 = prec != KM_TIME_EXTENDED;
+    const bool alone = 2 * quad_bytes > kMaxLds;
     if (n_traces <= 4 * 256) return 5;
-    if (kind == KIND_LTABLE) return n_traces >= 12 * 2048 ? 4 : prec == KM_TIME_EXTENDED ? 0 : 3;
-    if (kind == KIND_TABLE) return n_traces >= 12 * 1536 ? 1 : n_traces >= 12 * 256 ? 2 : 3;
-    return 3;
+    if (kind == KIND_LTABLE) return n_traces >= 12 * 2048 ? 4 : alone ? 2 : fp32 ? 3 : 0;
+    if (kind == KIND_TABLE) return n_traces >= 12 * 1536 ? 1 : n_traces >= 12 * 256 || alone ? 2 : 3;
+    if (kind == KIND_DSR && fp32) return alone ? 2 : 3 * quad_bytes > kMaxLds ? 0 : 3;
+    return alone ? 5 : 3;
 }
 
 // Whether a tile can run problems of a class: a tile of op, and a 16-bit
@@ -573,7 +594,8 @@ km_status demigrate_impl(const float* image, const km_grid* grid, const km_trave
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
     st = pick_tile(1, tile, out->dtype, kind, tt->time_precision, grid->nz, out->n_samples,
-                   [&] { return default_demigrate_tile(kind, tt->time_precision, out->n_traces); }, &shape);
+                   [&] { return default_demigrate_tile(kind, tt->time_precision, out->n_traces,
+                                                        quad_row_bytes(out->n_samples, aa)); }, &shape);
     if (st != KM_OK) return st;
     return run_op(1, out, grid, tt, weight, const_cast<float*>(image), accumulate, shape, s, tab, aa, lat);
 }

@@ -188,3 +188,27 @@ def test_adjoint_pairs_past_the_record(ops, n_t, t_first, weight, kind, spread):
     for tile in [-1] + list(range(ops.tile_count(1))):
         d = ops.demigrate(dp, m, tile=tile).cpu().numpy()
         assert np.all(np.abs(d - ref) <= 2.0 ** -22 * np.abs(ref) + 1e-9 * largest), tile
+
+
+# four float64 rows beside the small tables: within the shape's budget, up to and past two and one
+# workgroups per CU, up to the last record of which four fit, and where fewer do
+@pytest.mark.parametrize("n_t", [1500, 2530, 2560, 5090, 5110, 10300])
+@pytest.mark.parametrize("kind", ["fp32", "extended", "aa", "table"])
+def test_adjoint_rows_of_long_records(ops, oracle_lib, n_t, kind):
+    p = survey.make_random(n_t, 13, n_t, 9, 2, 40, 2, weight=survey.WEIGHT_UNIT, dt=0.0004)
+    if kind == "aa":
+        p = dataclasses.replace(p, aa=(12.0, 12.0, 8))
+    elif kind == "table":
+        p = survey.with_curved_ray_table(p, 10.0)
+    dp = ops.to_device(p, prec="extended" if kind == "extended" else "fp32")
+    m = survey.random_image(p, 3)
+    ref = ops.demigrate(dp, torch.from_numpy(m).cuda(), tile=1).cpu().numpy().astype(np.float64)
+    # the same taps in another order, float64: two roundings, 1e-9 for the anti-alias sums
+    for tile in [-1] + list(range(ops.tile_count(1))):
+        d = ops.demigrate(dp, torch.from_numpy(m).cuda(), tile=tile).cpu().numpy()
+        assert np.all(np.abs(d - ref) <= 2.0 ** -22 * np.abs(ref) + 1e-9 * np.abs(ref).max()), tile
+    # against the oracle: a float32 time of up to 10 300 samples is good to 3 x 2^-24 of itself, 2e-3 samples
+    data = survey.random_data(p, 4)
+    lhs = float(np.vdot(oracle_lib.migrate(dataclasses.replace(p, data=data)), m))
+    rhs = float(np.vdot(data.astype(np.float64), ref))
+    assert abs(lhs - rhs) <= 2e-3 * np.linalg.norm(data.astype(np.float64)) * np.linalg.norm(ref)
