@@ -415,11 +415,14 @@ int64_t migrate_workgroups(int shape, const km_grid& g) {
 // against 6.6 ms with tile 6 and 5.4 ms with tile 7 (table), 8.1 against 11.4
 // and 9.1 ms (anti-alias); 480 of them 6.9 ms against 5.5 ms with tile 7
 // (lateral tables).
-// Tile 2 (128 columns) where the grid of tile 5 would pass 2^32 threads.
+// Tile 2 (128 columns) with invariant tables from 8192 workgroups, where staging whole
+// records outweighs the finer tile (2.54 s against 2.86 s on 65 536 workgroups, 188
+// against 190 ms on 16 384; 163 against 158 ms on 32 768 shallower ones), and where the
+// grid of tile 5 would pass 2^32 threads.
 template <typename Workgroups>
 int default_migrate_tile(int kind, Workgroups workgroups) {
     const int64_t wide = workgroups(5);  // 64 columns x 128 depths
-    if (wide >= int64_t{1} << 22) return 2;
+    if (wide >= int64_t{1} << 22 || (kind == KIND_TABLE && wide >= 8192)) return 2;
     if (wide >= (kind == KIND_DSR ? 1024 : 512)) return 5;
     const int64_t n = workgroups(6);     // 16 columns x 128 depths, also of shape 7
     if (kind == KIND_DSR && n >= 400) return 6;
