@@ -533,9 +533,9 @@ __device__ __forceinline__ void demigrate_segment(const Params& P, int b, int t0
 }
 
 // The 4-slot square-root kernels are held to 6 wavefronts per SIMD (80 VGPRs;
-// the float32 kernel spills 3 registers in its set-up, outside the column
-// loop; the extended-precision one about 20, and ran 2.38 s against 2.56 s at
-// its natural 108 on the 3D survey): with 8-wavefront one-quad workgroups that
+// the float32 kernel fits without spills; the extended-precision one spills
+// about 20 in its set-up, outside the column loop, and ran 2.38 s against 2.56 s
+// at its natural 108 on the 3D survey): with 8-wavefront one-quad workgroups that
 // is three workgroups per CU, as many as their LDS rows allow.  The other
 // kernels need more registers.
 template <int NW, int KS, int NQ, bool TF, int WK, int TT = TT_DSR, bool PX = false>
