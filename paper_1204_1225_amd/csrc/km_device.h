@@ -875,15 +875,18 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int z
         float R = valid ? r2 : -1.0f;
         // only where the longest legs' time may pass the record's end (bounding every
         // slot cost small images 6 %)
-        if (CUT && __builtin_amdgcn_ballot_w64(valid && !(4.0f * fmaf(B, R, A) <= E.end * E.end)))
-            R = fminf(R, record_aperture(A, B, E));
+        if (CUT && __builtin_amdgcn_ballot_w64(valid && !(4.0f * fmaf(B, R, A) <= E.end * E.end))) {
+            const float cut = record_aperture(A, B, E);
+            R = cut < R ? cut : R;  // a NaN aperture stays one: it admits no pair
+        }
         T.A[k] = A;
         T.B[k] = B;
         T.R[k] = R;
         if (sR && lane < kGroup) sR[k * kGroup + d] = R;
         if ((__builtin_amdgcn_ballot_w64(valid) & 0xFFFFull) == 0xFFFFull) clean |= 1u << k;
         // min / max over the 16 lanes of the group (all groups hold the same depths)
-        float lo = valid ? R : __builtin_inff();
+        // (a valid lane whose aperture is NaN or negative admits nothing: its slot is never full)
+        float lo = valid ? fmaxf(R, -1.0f) : __builtin_inff();
         float hi = valid ? R : -__builtin_inff();
         lo = group_min(lo);
         hi = group_max(hi);

@@ -212,3 +212,29 @@ def test_adjoint_rows_of_long_records(ops, oracle_lib, n_t, kind):
     lhs = float(np.vdot(oracle_lib.migrate(dataclasses.replace(p, data=data)), m))
     rhs = float(np.vdot(data.astype(np.float64), ref))
     assert abs(lhs - rhs) <= 2e-3 * np.linalg.norm(data.astype(np.float64)) * np.linalg.norm(ref)
+
+
+# An aperture value that is NaN admits no pair (h^2 <= NaN is false), in both directions, also
+# where the record's end bounds the aperture or the slot's other depths are all inside: as -1 does.  The same taps in another
+# order: two roundings, 1e-9 of the largest for the anti-alias sums.
+@pytest.mark.parametrize("kind", ["fp32", "extended", "aa"])
+@pytest.mark.parametrize("flat", [False, True])  # s2 = 0 at those depths: no bound from the record's end
+def test_nan_aperture_admits_no_pair(ops, kind, flat):
+    p = survey.make_random(5, 45, 120, 21, 4, 90, 2, weight=survey.WEIGHT_UNIT)
+    deep = np.arange(p.nz) % 3 == 1
+    if flat:
+        p = dataclasses.replace(p, s2=np.where(deep, 0.0, p.s2))
+    if kind == "aa":
+        p = dataclasses.replace(p, aa=(12.0, 12.0, 8))
+    prec = "extended" if kind == "extended" else "fp32"
+    m = torch.from_numpy(survey.random_image(p, 6)).cuda()
+    none = ops.to_device(dataclasses.replace(p, r2=np.where(deep, -1.0, p.r2)), prec=prec)
+    nan = ops.to_device(dataclasses.replace(p, r2=np.where(deep, np.nan, p.r2)), prec=prec)
+    ref = ops.demigrate(none, m).cpu().numpy().astype(np.float64)
+    assert np.any(ref)
+    for tile in [-1] + list(range(ops.tile_count(1))):
+        d = ops.demigrate(nan, m, tile=tile).cpu().numpy()
+        assert np.all(np.abs(d - ref) <= 2.0 ** -22 * np.abs(ref) + 1e-9 * np.abs(ref).max()), tile
+    for tile in [-1] + list(range(ops.tile_count(0))):
+        img = ops.migrate(nan, tile=tile)
+        assert torch.equal(img, ops.migrate(none, tile=tile)) and torch.any(img), tile
