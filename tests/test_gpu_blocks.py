@@ -238,3 +238,35 @@ def test_nan_aperture_admits_no_pair(ops, kind, flat):
     for tile in [-1] + list(range(ops.tile_count(0))):
         img = ops.migrate(nan, tile=tile)
         assert torch.equal(img, ops.migrate(none, tile=tile)) and torch.any(img), tile
+
+
+# An infinite image value reaches the two samples around its pairs' times and no other: the
+# adjoint of one infinite point is non-finite there only, everything else as with a 0 in its place
+# (another summation order: two roundings).  A time within 2^-18 of a sample may count as that
+# sample, so a pair's two samples are those of the times a little to either side.
+@pytest.mark.parametrize("weight", [survey.WEIGHT_UNIT, survey.WEIGHT_COSCOS])
+@pytest.mark.parametrize("t_first", [0.0, 0.1])
+def test_adjoint_infinity_stays_within_its_taps(ops, weight, t_first):
+    p = survey.make_random(8, 37, 260, 15, 3, 70, 1, weight=weight, t_first=t_first, spread=100.0)
+    dp = ops.to_device(p)
+    m = survey.random_image(p, 9)
+    points = [(0, 1, 7, iz) for iz in range(20, 52)]  # both slots of every depth pair
+    hit = 0
+    for b, iy, ix, iz in points:
+        m0, m1 = m.copy(), m.copy()
+        m0[b, iy, ix, iz], m1[b, iy, ix, iz] = 0.0, np.inf
+        h2 = [((p.x[ix] - q[:, 0]) ** 2 + (p.y[iy] - q[:, 1]) ** 2).astype(np.float64) for q in (p.src, p.rec)]
+        u = (sum(np.sqrt(p.t0sq[iz] + p.s2[iz] * h) for h in h2) - t_first) / p.dt
+        inside = np.maximum(*h2) <= p.r2[iz] * (1.0 + 1e-5)
+        may = np.zeros((p.n_traces, p.n_t), bool)
+        for j in np.flatnonzero(inside):
+            for i in {int(np.floor(u[j] * (1.0 + e))) + k for e in (-1e-6, 1e-6) for k in (0, 1)}:
+                if 0 <= i < p.n_t:
+                    may[j, i] = True
+        ref = ops.demigrate(dp, torch.from_numpy(m0).cuda()).cpu().numpy().astype(np.float64)
+        d = ops.demigrate(dp, torch.from_numpy(m1).cuda()).cpu().numpy()
+        assert not np.any(~np.isfinite(d) & ~may), iz
+        ok = np.isfinite(d)
+        assert np.all(np.abs(d - ref)[ok] <= 2.0 ** -22 * np.abs(ref[ok]) + 1e-9 * np.abs(ref).max()), iz
+        hit += int(np.sum(~ok))
+    assert hit > 100
