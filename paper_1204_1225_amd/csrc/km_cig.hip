@@ -110,7 +110,9 @@ inline CigShape cig_choose(int n_bins, int nz, int L) {
 
 // Partial C_b(l) over depths [za, zb) for l = lag0 .. lag0 + LB - 1: slot
 // (u + j) % LB of the window holds row[z + u + lag0 + j].  Steps past zb use a
-// zero stack value.
+// zero stack value; where that meets an infinity or a NaN below the depth window
+// the sums are formed again without them (a guard around those steps instead:
+// 1.20 -> 1.23 ms on the 3D survey).
 template <int LB>
 __device__ __forceinline__ void lag_block(const double* sS, const float* row, int lag0, int za, int zb, double* c) {
     double w[LB];
@@ -127,6 +129,18 @@ __device__ __forceinline__ void lag_block(const double* sS, const float* row, in
             const double sv = (z + u < zb) ? sS[z + u] : 0.0;
 #pragma unroll
             for (int j = 0; j < LB; ++j) c[j] = fma(sv, w[(u + j) % LB], c[j]);
+        }
+    }
+    bool nan = false;
+#pragma unroll
+    for (int j = 0; j < LB; ++j) nan = nan || c[j] != c[j];
+    if (nan) {
+#pragma unroll
+        for (int j = 0; j < LB; ++j) c[j] = 0.0;
+#pragma unroll 1
+        for (int z = za; z < zb; ++z) {
+#pragma unroll
+            for (int j = 0; j < LB; ++j) c[j] = fma(sS[z], static_cast<double>(row[z + lag0 + j]), c[j]);
         }
     }
 }

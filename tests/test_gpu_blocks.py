@@ -270,3 +270,22 @@ def test_adjoint_infinity_stays_within_its_taps(ops, weight, t_first):
         assert np.all(np.abs(d - ref)[ok] <= 2.0 ** -22 * np.abs(ref[ok]) + 1e-9 * np.abs(ref).max()), iz
         hit += int(np.sum(~ok))
     assert hit > 100
+
+
+# Depths that no lag of the window reaches do not matter, whatever they hold (lags of one to
+# five blocks, windows that end inside a block's turn).
+@pytest.mark.parametrize("lag", [1, 4, 6, 12, 20, 40])
+@pytest.mark.parametrize("bins", [2, 16, 40])
+def test_moveout_window_shuts_out_other_depths(ops, lag, bins):
+    rng = np.random.default_rng(lag + bins)
+    nz, z_lo, z_hi = 200, 50, 90 + lag % 3
+    img = rng.standard_normal((bins, 1, 3, nz)).astype(np.float32)
+    out = np.r_[0:max(z_lo - lag, 0), z_hi + lag:nz]
+    off = torch.linspace(10.0, 900.0, bins, device="cuda")
+    img[..., out] = 0.0
+    ref = ops.cig_moveout(torch.from_numpy(img).cuda(), off, lag, z_lo, z_hi)
+    for v in (np.inf, np.nan):
+        img[..., out] = v
+        got = ops.cig_moveout(torch.from_numpy(img).cuda(), off, lag, z_lo, z_hi)
+        for a, b in zip(got[1:], ref[1:]):
+            assert torch.equal(a, b) and torch.isfinite(a).all(), v
