@@ -407,12 +407,12 @@ __device__ __forceinline__ void mig_slot_aa(float A, float B, float ss, float is
 }
 
 // The source legs of every slot from the leg's squared length (float32 and,
-// for the extended kernels, float64).  vd: byte offset of the lane's depth in
-// slot 0 of a table row.  Table slot pairs that no lane of the wavefront can use
+// for the extended kernels, float64).  vd, vl: byte offset of the lane's depth in
+// slot 0 of a table row, and how far it is to the table's last depth.  Table slot pairs that no lane of the wavefront can use
 // are not read (a pair is evaluated whole, so both its slots are filled).
 template <int KS, int WK, int TT, bool PX>
 __device__ __forceinline__ void source_leg(const Params& P, const ChunkTables<KS>& T, float hs2, double Hs, LCol C,
-                                           int vd, SrcLeg<KS, TT, PX>& S) {
+                                           int vd, int vl, SrcLeg<KS, TT, PX>& S) {
     if constexpr (is_table(TT)) {
         constexpr bool LAT = TT == TT_LTABLE;
         const float hmin = uniform_f(rows_min(hs2));
@@ -423,8 +423,8 @@ __device__ __forceinline__ void source_leg(const Params& P, const ChunkTables<KS
 #pragma unroll
             for (int k = 0; k < KS; ++k)
                 if ((any >> (k & ~1)) & 3ull) {
-                    S.t[k] = LAT ? ltable_time_ext_at(P, L.f, C, vb + 64 * k) : table_time_ext_at(P, L.f, vb + 64 * k);
-                    if (P.tamp) S.amp[k] = table_amp_at<LAT>(P, static_cast<float>(L.f), C, vb + 64 * k);
+                    S.t[k] = LAT ? ltable_time_ext_at(P, L.f, C, vb + min(64 * k, vl)) : table_time_ext_at(P, L.f, vb + min(64 * k, vl));
+                    if (P.tamp) S.amp[k] = table_amp_at<LAT>(P, static_cast<float>(L.f), C, vb + min(64 * k, vl));
                 }
         } else {
             const TLeg L = table_leg(P, hs2);
@@ -432,10 +432,10 @@ __device__ __forceinline__ void source_leg(const Params& P, const ChunkTables<KS
 #pragma unroll
             for (int k = 0; k < KS; ++k)
                 if ((any >> (k & ~1)) & 3ull) {
-                    const TTime t = LAT ? ltable_time_at(P, L.f, C, vb + 64 * k) : table_time_at(P, L.f, vb + 64 * k);
+                    const TTime t = LAT ? ltable_time_at(P, L.f, C, vb + min(64 * k, vl)) : table_time_at(P, L.f, vb + min(64 * k, vl));
                     S.base[k] = t.base;
                     S.inc[k] = t.inc;
-                    if (P.tamp) S.amp[k] = table_amp_at<LAT>(P, L.f, C, vb + 64 * k);
+                    if (P.tamp) S.amp[k] = table_amp_at<LAT>(P, L.f, C, vb + min(64 * k, vl));
                 }
         }
     } else if constexpr (PX) {
@@ -549,6 +549,8 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
     load_chunk_tables<KS, 1, TT, PX>(P, z0, z1, d, WK == W_COSCOS, T, sR);
 
     constexpr bool LAT = TT == TT_LTABLE;
+    // bytes from the lane's depth in slot 0 to the table's last: a lane past it reads that one
+    const int vl = 4 * (P.nz - 1 - z0 - d);
     // first column of the wavefront's groups; group q's lane column is col0 + 4 q + g
     const int col0 = (tile * NC + cw) * CWQ * kGroupsPerWave;
 
@@ -868,7 +870,7 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
                         }
                         double Hs = 0.0;
                         if (PX) Hs = bperm_d(row4 | 4 * tc, Lx.hs2);
-                        source_leg<KS, WK, TT, PX>(P, T, hs2, Hs, lc, 4 * (z0 + d), S);
+                        source_leg<KS, WK, TT, PX>(P, T, hs2, Hs, lc, 4 * (z0 + d), vl, S);
                     }
                     // max(hs2, hr2): one v_max (fmaxf would first quiet both inputs)
                     float hm;
@@ -889,8 +891,8 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
 #pragma unroll
                         for (int k = 0; k < KS; k += 2) {
                             if ((any >> k) & 3u) {
-                                const Pair p0 = pair_table_ext<TF, LAT>(P, S.t[k], S.amp[k], Lr.f, vr + 64 * k, wlo, whi, lc);
-                                const Pair p1 = pair_table_ext<TF, LAT>(P, S.t[k + 1], S.amp[k + 1], Lr.f, vr + 64 * k + 64, wlo, whi, lc);
+                                const Pair p0 = pair_table_ext<TF, LAT>(P, S.t[k], S.amp[k], Lr.f, vr + min(64 * k, vl), wlo, whi, lc);
+                                const Pair p1 = pair_table_ext<TF, LAT>(P, S.t[k + 1], S.amp[k + 1], Lr.f, vr + min(64 * k + 64, vl), wlo, whi, lc);
                                 const float a0 = row[p0.i], b0 = row[p0.i + 1];
                                 const float a1 = row[p1.i], b1 = row[p1.i + 1];
                                 mask_add2<W_COSCOS, KS, RREG>(T, sR, full, k, d, hm, fmaf(p0.f, b0 - a0, a0),
@@ -905,8 +907,8 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
 #pragma unroll
                         for (int k = 0; k < KS; k += 2) {
                             if ((any >> k) & 3u) {
-                                const Pair p0 = pair_table<TF, LAT>(P, TTime{S.base[k], S.inc[k]}, S.amp[k], Lr.f, vr + 64 * k, wlo, whi, lc);
-                                const Pair p1 = pair_table<TF, LAT>(P, TTime{S.base[k + 1], S.inc[k + 1]}, S.amp[k + 1], Lr.f, vr + 64 * k + 64, wlo, whi, lc);
+                                const Pair p0 = pair_table<TF, LAT>(P, TTime{S.base[k], S.inc[k]}, S.amp[k], Lr.f, vr + min(64 * k, vl), wlo, whi, lc);
+                                const Pair p1 = pair_table<TF, LAT>(P, TTime{S.base[k + 1], S.inc[k + 1]}, S.amp[k + 1], Lr.f, vr + min(64 * k + 64, vl), wlo, whi, lc);
                                 float a0, b0, a1, b1;
                                 if (S16) {
                                     widen_pair<S16>(read_pair16(sw, rb + p0.i), a0, b0);
