@@ -1030,8 +1030,8 @@ struct BatchPlan {
     int64_t n_slots = 0;      // items over all problems
 };
 
-// max_items: work items the caller has room for; the untuned choice takes the
-// largest tile where its own tile makes more.
+// max_items: work items the caller has room for; where the library's choice
+// makes more, a tuned tile gives way to the default and that to the largest tile.
 km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t max_items, const char* who,
                      BatchPlan& B) {
     if (!probs || n < 1) return fail(KM_E_INVALID, "%s: need n >= 1 problems", who);
@@ -1059,13 +1059,15 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
         for (int i = 0; i < n; ++i) w += migrate_workgroups(sh, probs[i].grid);
         return w;
     };
+    const auto fits = [&](int t) { return workgroups(t % kTileLevelStride) <= max_items; };
+    const auto untuned = [&] {
+        const int t = default_migrate_tile(KIND_DSR, workgroups);
+        return fits(t) ? t : 2;
+    };
     km_status st = pick_tile(0, tile, probs[0].traces.dtype, KIND_DSR, probs[0].tt.time_precision, max_nz, max_nt,
-                             [&] {
-                                 const int t = default_migrate_tile(KIND_DSR, workgroups);
-                                 return workgroups(t % kTileLevelStride) > max_items ? 2 : t;
-                             },
-                             &B.tile);
+                             untuned, &B.tile);
     if (st != KM_OK) return st;
+    if (tile < 0 && !fits(B.tile)) B.tile = untuned();
     B.shape = B.tile % kTileLevelStride;
     {
         // the batched kernels stage floats: a tuned 16-bit staging tile becomes
