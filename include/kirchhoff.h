@@ -384,14 +384,16 @@ km_status km_tile_describe(int32_t op, int32_t tile, km_tile_info* out /* host *
 /* Autotuner: time every tile (compiled shape x level) of op on this problem
  * (each run once untimed, then `reps` times), keep the fastest for the
  * problem's class (GPU architecture, op, dtype, traveltime kind, time
- * precision, nz / 128, n_samples / 512) and return it; calls with tile = -1
- * then use it.  table (table traveltimes; tt is then ignored and W = 1) or aa
+ * precision, nz / 128, n_samples / 512) and size (the power of two of
+ * nx ny n_bins for migrate, of n_traces for demigrate), and return it; calls of
+ * that class and size with tile = -1 then use it.  table (table traveltimes; tt is then ignored and W = 1) or aa
  * (anti-alias filter) may be NULL, not both non-NULL.  Synchronises the
  * stream.  Writes the output buffer (image for op 0, traces->data for op 1)
  * with accumulate = 0 semantics.  best_tile, best_ms: host, may be NULL.
  * The class cache is kept per process and, when the environment variable
  * KM_TUNE_CACHE names a file, read from it at first use and rewritten (JSON)
- * after every record, so a later process starts tuned. */
+ * after every record, so a later process starts tuned.  Entries of a file of
+ * version 1, which had no sizes, are taken for every size of their class. */
 km_status km_tune(int32_t op, const km_traces* traces, const km_grid* grid, const km_traveltime* tt,
                   const km_weight* weight, const km_ttable* table, const km_antialias* aa, float* image,
                   int32_t reps, void* stream, int32_t* best_tile /* host */, float* best_ms /* host */);
@@ -403,8 +405,9 @@ km_status km_tune_ltable(int32_t op, const km_traces* traces, const km_grid* gri
                          float* best_ms /* host */);
 
 /* The class cache of km_tune.  kind: 0 = square-root times, 1 = table times,
- * 2 = anti-alias filter, 3 = laterally varying tables.  km_tune_lookup returns -1 when nothing is recorded;
- * km_tune_record stores (and persists) a tile with its time, and returns KM_E_INVALID for a tile out of range
+ * 2 = anti-alias filter, 3 = laterally varying tables.  km_tune_lookup returns the tile recorded last for the
+ * class, of whatever size, and -1 when nothing is recorded; km_tune_record stores (and persists) a tile with its
+ * time for every size of the class, in place of what the class held, and returns KM_E_INVALID for a tile out of range
  * or a 16-bit staging tile (migrate levels 4, 5) for a class of KM_F32 traces, KM_TIME_EXTENDED or kind 2.
  * Calls with tile = -1 take a recorded tile only if it applies to their class (a cache file may come from
  * another build); otherwise the library's default. */

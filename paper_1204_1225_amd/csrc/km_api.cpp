@@ -270,26 +270,39 @@ km_status shape_params(int op, int tile, km::Params& P) {
 
 // ---- tuning cache ----------------------------------------------------------
 // Keyed by (GPU architecture, op, dtype, traveltime kind, time precision,
-// depth bucket nz / 128, sample bucket n_samples / 512); persisted as JSON to
-// the file named by the KM_TUNE_CACHE environment variable (read on first
+// depth bucket nz / 128, sample bucket n_samples / 512) and a size bucket: the
+// best tile depends most on how far a problem fills the chip.  Persisted as JSON
+// to the file named by the KM_TUNE_CACHE environment variable (read on first
 // use, rewritten after every record).
 struct TuneKey {
     std::string arch;
     int op, dtype, kind, prec, nzb, ntb;
+    int size;  // size_bucket of the tuned problem, or kAnySize
     bool operator<(const TuneKey& o) const {
-        return std::tie(arch, op, dtype, kind, prec, nzb, ntb) <
-               std::tie(o.arch, o.op, o.dtype, o.kind, o.prec, o.nzb, o.ntb);
+        return std::tie(arch, op, dtype, kind, prec, nzb, ntb, size) <
+               std::tie(o.arch, o.op, o.dtype, o.kind, o.prec, o.nzb, o.ntb, o.size);
+    }
+    bool same_class(const TuneKey& o) const {
+        TuneKey k = o;
+        k.size = size;
+        return !(*this < k) && !(k < *this);
     }
 };
+
+// A tile recorded by hand (km_tune_record), or in a file of version 1, which had no
+// sizes: for every problem of its class that has no tile of its own size.
+constexpr int kAnySize = -1;
 
 struct TuneEntry {
     int tile;
     float ms;
+    int64_t order;  // when it was recorded: a class's last is what km_tune_lookup gives
 };
 
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneEntry> g_tune;
 bool g_tune_loaded = false;
+int64_t g_tune_order = 0;
 
 // Architecture of the current device ("gfx950"), or "unknown" without one.
 std::string device_arch() {
@@ -304,9 +317,21 @@ std::string device_arch() {
     return c == std::string::npos ? a : a.substr(0, c);
 }
 
-TuneKey tune_key(int op, int dtype, int kind, int prec, int nz, int nt) {
-    return TuneKey{device_arch(), op, dtype, kind, prec, (nz + 127) / 128, (nt + 511) / 512};
+TuneKey tune_key(int op, int dtype, int kind, int prec, int nz, int nt, int size) {
+    return TuneKey{device_arch(), op, dtype, kind, prec, (nz + 127) / 128, (nt + 511) / 512, size};
 }
+
+// Powers of two: of the image columns times bins (migrate) or of the traces
+// (demigrate), what a problem's workgroups are counted in beside its depth bucket.
+int size_bucket(int64_t n) {
+    int b = 0;
+    while (n > 1) {
+        n >>= 1;
+        ++b;
+    }
+    return b;
+}
+int64_t image_columns(const km_grid& g) { return static_cast<int64_t>(g.nx) * g.ny * g.n_bins; }
 
 const char* tune_cache_path() {
     const char* p = std::getenv("KM_TUNE_CACHE");
@@ -360,11 +385,13 @@ void tune_load_locked() {
         for (int k = 0; k < 9 && ok; ++k) ok = json_field(obj, names[k], &v[k]);
         if (!ok) continue;
         TuneKey key{v[0], std::atoi(v[1].c_str()), std::atoi(v[2].c_str()), std::atoi(v[3].c_str()),
-                    std::atoi(v[4].c_str()), std::atoi(v[5].c_str()), std::atoi(v[6].c_str())};
+                    std::atoi(v[4].c_str()), std::atoi(v[5].c_str()), std::atoi(v[6].c_str()), kAnySize};
+        std::string size;
+        if (json_field(obj, "size_bucket", &size)) key.size = std::atoi(size.c_str());
         int shape = 0, level = 0;
         const int tile = std::atoi(v[7].c_str());
         if ((key.op == 0 || key.op == 1) && decode_tile(key.op, tile, &shape, &level))
-            g_tune[key] = TuneEntry{tile, static_cast<float>(std::atof(v[8].c_str()))};
+            g_tune[key] = TuneEntry{tile, static_cast<float>(std::atof(v[8].c_str())), ++g_tune_order};
     }
 }
 
@@ -374,15 +401,18 @@ void tune_save_locked() {
     const std::string tmp = std::string(path) + ".tmp";
     FILE* f = std::fopen(tmp.c_str(), "wb");
     if (!f) return;
-    std::fprintf(f, "{\n  \"format\": \"km_tune_cache\",\n  \"version\": 1,\n  \"entries\": [");
+    std::fprintf(f, "{\n  \"format\": \"km_tune_cache\",\n  \"version\": 2,\n  \"entries\": [");
+    std::vector<const std::pair<const TuneKey, TuneEntry>*> entries;  // as they were recorded
+    for (const auto& kv : g_tune) entries.push_back(&kv);
+    std::sort(entries.begin(), entries.end(), [](auto* a, auto* b) { return a->second.order < b->second.order; });
     bool first = true;
-    for (const auto& kv : g_tune) {
-        const TuneKey& k = kv.first;
+    for (const auto* kv : entries) {
+        const TuneKey& k = kv->first;
         std::fprintf(f,
                      "%s\n    {\"arch\": \"%s\", \"op\": %d, \"dtype\": %d, \"kind\": %d, \"precision\": %d, "
-                     "\"nz_bucket\": %d, \"nt_bucket\": %d, \"tile\": %d, \"ms\": %.4f}",
-                     first ? "" : ",", k.arch.c_str(), k.op, k.dtype, k.kind, k.prec, k.nzb, k.ntb, kv.second.tile,
-                     static_cast<double>(kv.second.ms));
+                     "\"nz_bucket\": %d, \"nt_bucket\": %d, \"size_bucket\": %d, \"tile\": %d, \"ms\": %.4f}",
+                     first ? "" : ",", k.arch.c_str(), k.op, k.dtype, k.kind, k.prec, k.nzb, k.ntb, k.size,
+                     kv->second.tile, static_cast<double>(kv->second.ms));
         first = false;
     }
     std::fprintf(f, "\n  ]\n}\n");
@@ -462,11 +492,13 @@ bool tile_applies(int op, int tile, int dtype, int kind, int prec) {
     return true;
 }
 
-// The caller's tile, else the tuned tile of this problem's class (if it still
-// applies: a cache file may come from another build), else the default.
+// The caller's tile, else the tuned tile of this problem's class and size, else
+// of its class (if it still applies: a cache file may come from another build),
+// else the default.  size: image columns times bins, or traces (demigrate).
 // default_tile: a function that gives the default.
 template <typename Default>
-km_status pick_tile(int op, int tile, int dtype, int kind, int prec, int nz, int nt, Default default_tile, int* out) {
+km_status pick_tile(int op, int tile, int dtype, int kind, int prec, int nz, int nt, int64_t size,
+                    Default default_tile, int* out) {
     if (tile >= 0) {
         int shape = 0, level = 0;
         if (!decode_tile(op, tile, &shape, &level))
@@ -476,10 +508,12 @@ km_status pick_tile(int op, int tile, int dtype, int kind, int prec, int nz, int
         return KM_OK;
     }
     {
-        const TuneKey key = tune_key(op, dtype, kind, prec, nz, nt);
+        TuneKey key = tune_key(op, dtype, kind, prec, nz, nt, size_bucket(size));
         std::lock_guard<std::mutex> lk(g_tune_mu);
         tune_load_locked();
         auto it = g_tune.find(key);
+        key.size = kAnySize;
+        if (it == g_tune.end()) it = g_tune.find(key);
         if (it != g_tune.end() && tile_applies(op, it->second.tile, dtype, kind, prec)) {
             *out = it->second.tile;
             return KM_OK;
@@ -566,7 +600,7 @@ km_status migrate_impl(const km_traces* traces, const km_grid* grid, const km_tr
     if (!image || !aligned(image, 4)) return fail(KM_E_INVALID, "kirchhoff_migrate: image is NULL or misaligned");
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
-    st = pick_tile(0, tile, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples,
+    st = pick_tile(0, tile, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples, image_columns(*grid),
                    [&] { return default_migrate_tile(kind, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
                    &shape);
     if (st != KM_OK) return st;
@@ -596,7 +630,7 @@ km_status demigrate_impl(const float* image, const km_grid* grid, const km_trave
     if (!image || !aligned(image, 4)) return fail(KM_E_INVALID, "kirchhoff_demigrate: image is NULL or misaligned");
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
-    st = pick_tile(1, tile, out->dtype, kind, tt->time_precision, grid->nz, out->n_samples,
+    st = pick_tile(1, tile, out->dtype, kind, tt->time_precision, grid->nz, out->n_samples, out->n_traces,
                    [&] { return default_demigrate_tile(kind, tt->time_precision, out->n_traces,
                                                         quad_row_bytes(out->n_samples, aa)); }, &shape);
     if (st != KM_OK) return st;
@@ -883,29 +917,40 @@ km_status km_tile_describe(int32_t op, int32_t tile, km_tile_info* out) {
     return KM_OK;
 }
 
+// The tile of the class that was recorded last, whatever its size.
 int32_t km_tune_lookup(int32_t op, int32_t dtype, int32_t kind, int32_t time_precision, int32_t nz,
                        int32_t n_samples) {
-    const TuneKey key = tune_key(op, dtype, kind, time_precision, nz, n_samples);
+    const TuneKey key = tune_key(op, dtype, kind, time_precision, nz, n_samples, kAnySize);
     std::lock_guard<std::mutex> lk(g_tune_mu);
     tune_load_locked();
-    auto it = g_tune.find(key);
-    return it == g_tune.end() ? -1 : it->second.tile;
+    const TuneEntry* last = nullptr;
+    for (const auto& kv : g_tune)
+        if (key.same_class(kv.first) && (!last || kv.second.order > last->order)) last = &kv.second;
+    return last ? last->tile : -1;
 }
 
-km_status km_tune_record(int32_t op, int32_t dtype, int32_t kind, int32_t time_precision, int32_t nz,
-                         int32_t n_samples, int32_t tile, float ms) {
+// size: size_bucket of the problem, or kAnySize, which replaces the whole class.
+static km_status tune_record(int32_t op, int32_t dtype, int32_t kind, int32_t time_precision, int32_t nz,
+                             int32_t n_samples, int size, int32_t tile, float ms) {
     if (op != 0 && op != 1) return fail(KM_E_INVALID, "km_tune_record: op must be 0 or 1");
     if (kind < KIND_DSR || kind > KIND_LTABLE) return fail(KM_E_INVALID, "km_tune_record: unknown kind %d", kind);
     int shape = 0, level = 0;
     if (!decode_tile(op, tile, &shape, &level)) return fail(KM_E_INVALID, "km_tune_record: tile out of range");
     if (!tile_applies(op, tile, dtype, kind, time_precision))
         return fail(KM_E_INVALID, "km_tune_record: tile %d stages 16-bit traces, which this class does not have", tile);
-    const TuneKey key = tune_key(op, dtype, kind, time_precision, nz, n_samples);
+    const TuneKey key = tune_key(op, dtype, kind, time_precision, nz, n_samples, size);
     std::lock_guard<std::mutex> lk(g_tune_mu);
     tune_load_locked();
-    g_tune[key] = TuneEntry{tile, ms};
+    if (size == kAnySize)
+        for (auto it = g_tune.begin(); it != g_tune.end();) it = key.same_class(it->first) ? g_tune.erase(it) : ++it;
+    g_tune[key] = TuneEntry{tile, ms, ++g_tune_order};
     tune_save_locked();
     return KM_OK;
+}
+
+km_status km_tune_record(int32_t op, int32_t dtype, int32_t kind, int32_t time_precision, int32_t nz,
+                         int32_t n_samples, int32_t tile, float ms) {
+    return tune_record(op, dtype, kind, time_precision, nz, n_samples, kAnySize, tile, ms);
 }
 
 // km_tune and km_tune_ltable: lat (with table) selects the laterally varying tables.
@@ -989,7 +1034,8 @@ static km_status tune_impl(int32_t op, const km_traces* traces, const km_grid* g
     hipEventDestroy(e1);
     if (st != KM_OK) return st;
     if (best < 0) return fail(KM_E_UNSUPPORTED, "km_tune: no tile fits this problem");
-    st = km_tune_record(op, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples, best, best_t);
+    st = tune_record(op, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples,
+                     size_bucket(op == 0 ? image_columns(*grid) : traces->n_traces), best, best_t);
     if (st != KM_OK) return st;
     if (best_tile) *best_tile = best;
     if (best_ms) *best_ms = best_t;
@@ -1050,7 +1096,9 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
                         who);
     }
     int max_nz = 0, max_nt = 0;
+    int64_t columns = 0;
     for (int i = 0; i < n; ++i) {
+        columns += image_columns(probs[i].grid);
         max_nz = std::max(max_nz, probs[i].grid.nz);
         max_nt = std::max(max_nt, probs[i].traces.n_samples);
     }
@@ -1065,7 +1113,7 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
         return fits(t) ? t : 2;
     };
     km_status st = pick_tile(0, tile, probs[0].traces.dtype, KIND_DSR, probs[0].tt.time_precision, max_nz, max_nt,
-                             untuned, &B.tile);
+                             columns, untuned, &B.tile);
     if (st != KM_OK) return st;
     if (tile < 0 && !fits(B.tile)) B.tile = untuned();
     B.shape = B.tile % kTileLevelStride;

@@ -2,6 +2,7 @@
 pointers are never used).  Each check runs in a process of its own without
 devices; KM_FAULT_INJECT=launch makes a call that reaches its launch return
 KM_E_HIP."""
+import json
 import os
 import subprocess
 import sys
@@ -49,3 +50,50 @@ assert lib.km_tune_record(0, 0, 0, 0, 1000, 500, 8, 1.0) == _lib.KM_OK
 assert static_batch(8, **big) == _lib.KM_E_UNSUPPORTED and said("work items")  # asked for: refused
 assert static_batch(-1, **big) == _lib.KM_E_HIP, lib.km_last_error()
 """)
+
+
+DEEP = "deep = dict(n_t=500, nz=5000000)\n"  # tile 8 holds 64 depths: more chunks than a launch has
+
+
+def entry(tile, size=None, op=0, ntb=1, nzb=39063):
+    e = dict(arch="unknown", op=op, dtype=0, kind=0, precision=0, nz_bucket=nzb, nt_bucket=ntb, tile=tile, ms=1.0)
+    return e if size is None else dict(e, size_bucket=size)
+
+
+def cache(tmp_path, version, *entries):
+    path = tmp_path / "tune.json"
+    path.write_text(json.dumps({"format": "km_tune_cache", "version": version, "entries": list(entries)}))
+    return path
+
+
+def test_tuned_tile_is_for_its_size(tmp_path):
+    # a tile tuned on 2 columns x 1 bin (size bucket 1) is taken there and not on 16 columns
+    path = cache(tmp_path, 2, entry(8, 1))
+    run(DEEP + """
+assert migrate(nx=2, **deep) == _lib.KM_E_UNSUPPORTED and said("depth chunks")
+assert migrate(nx=16, **deep) == _lib.KM_E_HIP and said("injected")
+assert migrate(nx=2, bins=8, **deep) == _lib.KM_E_HIP and said("injected")
+assert lib.km_tune_lookup(0, 0, 0, 0, 5000000, 500) == 8
+""", KM_TUNE_CACHE=path)
+    # the adjoint's size is its traces: a tile of no shape that holds 65535 x 64 depths at 4 traces only
+    path = cache(tmp_path, 2, entry(3, 2, op=1))
+    run(DEEP + """
+assert demigrate(n=4, **deep) == _lib.KM_E_UNSUPPORTED and said("depth chunks")
+assert lib.km_tune_record(1, 0, 0, 0, 5000000, 500, 0, 1.0) == _lib.KM_OK  # every size, in its place
+assert demigrate(n=4, **deep) == _lib.KM_E_HIP and demigrate(n=400, **deep) == _lib.KM_E_HIP
+""", KM_TUNE_CACHE=path)
+    assert [(e["tile"], e["size_bucket"]) for e in json.loads(path.read_text())["entries"]] == [(0, -1)]
+
+
+def test_tuned_tile_without_a_size_is_for_its_class(tmp_path):
+    # a file of version 1, and beside it a tile of one size
+    path = cache(tmp_path, 1, entry(8))
+    run(DEEP + """
+for nx in (2, 16, 300): assert migrate(nx=nx, **deep) == _lib.KM_E_UNSUPPORTED and said("depth chunks")
+""", KM_TUNE_CACHE=path)
+    path = cache(tmp_path, 2, entry(8, -1), entry(2, 4))
+    run(DEEP + """
+assert migrate(nx=2, **deep) == _lib.KM_E_UNSUPPORTED and said("depth chunks")
+assert migrate(nx=16, **deep) == _lib.KM_E_HIP and said("injected")
+assert lib.km_tune_lookup(0, 0, 0, 0, 5000000, 500) == 2  # recorded last
+""", KM_TUNE_CACHE=path)
