@@ -52,6 +52,7 @@ km_status injected(const char* what) {
 }
 
 constexpr int kMaxLds = 160 * 1024;  // LDS per workgroup on gfx950
+constexpr int kBatchLds = kMaxLds - 16;  // the same beside the batch kernel's own variable
 constexpr int kMaxTracesPerBlock = 32;
 constexpr int kTailPad = 2;
 
@@ -171,7 +172,7 @@ int traces_per_block(int lt, int budget, int ks, int row_bytes_per_sample) {
 // slots for the longest records.  Sets P.tb and P.cap (floats); false if a
 // record does not fit in LDS.
 constexpr int kMigrateSlots = 128;
-bool migrate_block_params(km::Params& P, int budget, int ks, int waves) {
+bool migrate_block_params(km::Params& P, int budget, int ks, int waves, int limit) {
     // square-root times stage (sample, difference) pairs, table times samples,
     // 16-bit staging packed pairs of 16-bit samples and 16-bit samples (half
     // as many bytes), anti-aliasing float64 running sums over nt + 4 max_half
@@ -186,7 +187,7 @@ bool migrate_block_params(km::Params& P, int budget, int ks, int waves) {
         for (int tb = kMigrateSlots; tb >= 1; tb /= 2) {
             const int64_t fixed = static_cast<int64_t>(km::migrate_lds_words(0, tb, ks, P.list_cap));
             const int64_t cap = std::max<int64_t>((budget / 4 - fixed) & ~int64_t{3}, need);
-            if ((fixed + cap) * 4 <= kMaxLds) {
+            if ((fixed + cap) * 4 <= limit) {
                 P.tb = tb;
                 P.cap = static_cast<int>(cap);
                 return true;
@@ -228,7 +229,8 @@ bool decode_tile(int op, int tile, int* shape, int* level) {
     return true;
 }
 
-km_status shape_params(int op, int tile, km::Params& P) {
+// lds: LDS a migrate workgroup may take.
+km_status shape_params(int op, int tile, km::Params& P, int lds = kMaxLds) {
     int shape = 0, level = 0;
     if (!decode_tile(op, tile, &shape, &level)) return fail(KM_E_INVALID, "tile %d is not a tile of op %d", tile, op);
     const km::TileShape& S = op == 0 ? km::migrate_shape(shape) : km::demigrate_shape(shape);
@@ -238,8 +240,8 @@ km_status shape_params(int op, int tile, km::Params& P) {
             return fail(KM_E_UNSUPPORTED,
                         "tile %d stages 16-bit traces: it needs KM_BF16 or KM_F16 traces, float32 time precision "
                         "and no anti-alias filter", tile);
-        const int budget = static_cast<int>(std::min<double>(kMaxLds, S.lds_budget * kMigrateBudgetScale[level]));
-        if (!migrate_block_params(P, budget, S.depth_slots, S.waves)) P.tb = 0;
+        const int budget = static_cast<int>(std::min<double>(lds, S.lds_budget * kMigrateBudgetScale[level]));
+        if (!migrate_block_params(P, budget, S.depth_slots, S.waves, lds)) P.tb = 0;
     } else {
         // float64 rows; the four groups of a wavefront take four traces, so
         // whole quads of traces keep every group busy
@@ -1134,7 +1136,7 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
     for (int i = 0; i < n; ++i) {
         km::Params& P = B.P[i];
         P = base_params(&probs[i].traces, &probs[i].grid, &probs[i].tt, &probs[i].weight, probs[i].image, 0);
-        st = shape_params(0, B.tile, P);
+        st = shape_params(0, B.tile, P, kBatchLds);
         if (st != KM_OK) return st;
         if (P.n_traces > INT32_MAX)
             return fail(KM_E_UNSUPPORTED, "%s: problem %d has more than 2^31 - 1 traces", who, i);

@@ -289,3 +289,19 @@ def test_moveout_window_shuts_out_other_depths(ops, lag, bins):
         got = ops.cig_moveout(torch.from_numpy(img).cuda(), off, lag, z_lo, z_hi)
         for a, b in zip(got[1:], ref[1:]):
             assert torch.equal(a, b) and torch.isfinite(a).all(), v
+
+
+# Records whose trace block would take the whole of a workgroup's LDS: the batch kernel keeps a
+# variable of its own there.  One batch per tile, the same bits as the single launch.
+@pytest.mark.parametrize("n_t", [19764, 19796, 19956])
+def test_batches_of_the_longest_records(ops, n_t):
+    p = survey.make_random(n_t, 20, n_t, 9, 1, 40, 1, weight=survey.WEIGHT_UNIT, dt=0.0002, spread=50.0)
+    dp = ops.to_device(p)
+    for tile in [-1, 1 + 64 * 3] + list(range(ops.tile_count(0))):
+        img = torch.full(dp.image_shape, float("nan"), device="cuda")
+        b = ops.Batch([dp], [img], tile=tile)
+        b.run()
+        torch.cuda.synchronize()
+        b.close()
+        ref = ops.migrate(dp, tile=tile)
+        assert bool(torch.equal(img, ref)) and bool(torch.any(img)), tile
