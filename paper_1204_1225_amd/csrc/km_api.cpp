@@ -229,6 +229,8 @@ bool decode_tile(int op, int tile, int* shape, int* level) {
     return true;
 }
 
+constexpr int kMaxChunks = 65535;  // depth chunks of an image
+
 // lds: LDS a migrate workgroup may take.
 km_status shape_params(int op, int tile, km::Params& P, int lds = kMaxLds) {
     int shape = 0, level = 0;
@@ -263,7 +265,8 @@ km_status shape_params(int op, int tile, km::Params& P, int lds = kMaxLds) {
     // migrate: equal chunks of whole slot pairs
     const int pairs = (P.nz + 31) / 32;
     P.zspan = P.n_zchunks > 0 ? 32 * ((pairs + P.n_zchunks - 1) / P.n_zchunks) : zchunk;
-    if (P.n_zchunks > 65535) return fail(KM_E_UNSUPPORTED, "nz = %d needs more than 65535 depth chunks", P.nz);
+    if (P.n_zchunks > kMaxChunks)
+        return fail(KM_E_UNSUPPORTED, "nz = %d needs more than %d depth chunks", P.nz, kMaxChunks);
     const int cols = tile_columns(S);
     const int ncol = P.nx * P.ny;
     P.n_coltiles = (ncol + cols - 1) / cols;
@@ -450,9 +453,11 @@ int64_t migrate_workgroups(int shape, const km_grid& g) {
 // Tile 2 (128 columns) with invariant tables from 8192 workgroups, where staging whole
 // records outweighs the finer tile (2.54 s against 2.86 s on 65 536 workgroups, 188
 // against 190 ms on 16 384; 163 against 158 ms on 32 768 shallower ones), and where the
-// grid of tile 5 would pass 2^32 threads.
+// grid of tile 5 would pass 2^32 threads.  Depths that need more than kMaxChunks
+// chunks of 128 take chunks of 256 with laterally varying tables.
 template <typename Workgroups>
-int default_migrate_tile(int kind, Workgroups workgroups) {
+int default_migrate_tile(int kind, int nz, Workgroups workgroups) {
+    if (kind == KIND_LTABLE && nz > 128 * kMaxChunks) return 3;
     const int64_t wide = workgroups(5);  // 64 columns x 128 depths
     if (wide >= int64_t{1} << 22 || (kind == KIND_TABLE && wide >= 8192)) return 2;
     if (wide >= (kind == KIND_DSR ? 1024 : 512)) return 5;
@@ -474,7 +479,9 @@ int default_migrate_tile(int kind, Workgroups workgroups) {
 // slots (0.43 ms against 0.45 ms on 2400 samples; three workgroups of 1600
 // samples 0.40 ms with 4 slots against 0.42 ms), and where one fills it, 16 waves (0.49
 // ms against 0.65 ms on 3000 samples; extended times, 4 slots: 0.69 ms against 0.77 ms).
-int default_demigrate_tile(int kind, int prec, int64_t n_traces, int64_t quad_bytes) {
+// Depths that need more than kMaxChunks chunks of 4 slots take 8 slots with tables.
+int default_demigrate_tile(int kind, int prec, int nz, int64_t n_traces, int64_t quad_bytes) {
+    if (nz > 64 * kMaxChunks && (kind == KIND_TABLE || kind == KIND_LTABLE)) return kind == KIND_TABLE ? 1 : 4;
     const bool fp32 = prec != KM_TIME_EXTENDED;
     const bool alone = 2 * quad_bytes > kMaxLds;
     if (n_traces <= 4 * 256) return 5;
@@ -603,7 +610,7 @@ km_status migrate_impl(const km_traces* traces, const km_grid* grid, const km_tr
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
     st = pick_tile(0, tile, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples, image_columns(*grid),
-                   [&] { return default_migrate_tile(kind, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
+                   [&] { return default_migrate_tile(kind, grid->nz, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
                    &shape);
     if (st != KM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -633,7 +640,7 @@ km_status demigrate_impl(const float* image, const km_grid* grid, const km_trave
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
     st = pick_tile(1, tile, out->dtype, kind, tt->time_precision, grid->nz, out->n_samples, out->n_traces,
-                   [&] { return default_demigrate_tile(kind, tt->time_precision, out->n_traces,
+                   [&] { return default_demigrate_tile(kind, tt->time_precision, grid->nz, out->n_traces,
                                                         quad_row_bytes(out->n_samples, aa)); }, &shape);
     if (st != KM_OK) return st;
     return run_op(1, out, grid, tt, weight, const_cast<float*>(image), accumulate, shape, s, tab, aa, lat);
@@ -1111,7 +1118,7 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
     };
     const auto fits = [&](int t) { return workgroups(t % kTileLevelStride) <= max_items; };
     const auto untuned = [&] {
-        const int t = default_migrate_tile(KIND_DSR, workgroups);
+        const int t = default_migrate_tile(KIND_DSR, max_nz, workgroups);
         return fits(t) ? t : 2;
     };
     km_status st = pick_tile(0, tile, probs[0].traces.dtype, KIND_DSR, probs[0].tt.time_precision, max_nz, max_nt,

@@ -30,6 +30,17 @@ def static_batch(tile=-1, **kw):
     t, g, tt, w = args(**kw)
     pr = (_lib.KmProblem * 1)(_lib.KmProblem(traces=t, grid=g, tt=tt, weight=w, image=p))
     return lib.km_batch_migrate_static(pr, 1, tile, None)
+def tables(nz, n, grid=None):
+    # (migrate, demigrate) through one-way time tables of 2 rows, on a node grid or invariant
+    t, g, tt, w = args(n=n, nz=nz, n_t=500)
+    if grid:
+        tab = _lib.KmLtable(n_gx=1, n_gy=1, gx0=0.0, gy0=0.0, gdx=1.0, gdy=1.0, n_h=2, dh=10.0, t=p, r2=p)
+        names = lib.kirchhoff_migrate_ltable, lib.kirchhoff_demigrate_ltable
+    else:
+        tab = _lib.KmTtable(n_h=2, dh=10.0, t=p, r2=p)
+        names = lib.kirchhoff_migrate_table, lib.kirchhoff_demigrate_table
+    G, T, X = ctypes.byref(g), ctypes.byref(tab), ctypes.byref(t)
+    return names[0](X, G, T, p, 0, -1, None), names[1](p, G, T, X, 0, -1, None)
 def said(text): return text in lib.km_last_error().decode()
 """
 
@@ -97,3 +108,15 @@ assert migrate(nx=2, **deep) == _lib.KM_E_UNSUPPORTED and said("depth chunks")
 assert migrate(nx=16, **deep) == _lib.KM_E_HIP and said("injected")
 assert lib.km_tune_lookup(0, 0, 0, 0, 5000000, 500) == 2  # recorded last
 """, KM_TUNE_CACHE=path)
+
+
+def test_deep_tables_keep_their_chunks():
+    # 65535 chunks of 128 depths (migrate: 256 with lateral tables) whatever the number of traces
+    run("""
+for n in (4, 1500, 5000, 20000, 30000):
+    assert tables(8300000, n) == (_lib.KM_E_HIP, _lib.KM_E_HIP), n
+    assert tables(8300000, n, grid=True) == (_lib.KM_E_HIP, _lib.KM_E_HIP), n
+    assert tables(9000000, n) == (_lib.KM_E_UNSUPPORTED, _lib.KM_E_UNSUPPORTED), n
+    assert tables(16700000, n, grid=True) == (_lib.KM_E_HIP, _lib.KM_E_UNSUPPORTED), n
+    assert tables(16800000, n, grid=True) == (_lib.KM_E_UNSUPPORTED, _lib.KM_E_UNSUPPORTED), n
+""")
