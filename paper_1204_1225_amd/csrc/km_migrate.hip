@@ -486,6 +486,18 @@ __device__ __forceinline__ Pair pair_table_ext(const Params& P, double ts, float
     return p;
 }
 
+// Whether at least half of the traces [lo, hi) have the source of the trace before
+// them, from 64 places among them (one wavefront; the same answer in all).
+__device__ __forceinline__ bool sources_repeat(const Params& P, int64_t lo, int64_t hi) {
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int64_t j = lo + (hi - lo) * lane / kLanes;
+    const bool has = j + 1 < hi;
+    bool same = false;
+    if (has) same = P.src[2 * j] == P.src[2 * j + 2] && P.src[2 * j + 1] == P.src[2 * j + 3];
+    return 2 * __builtin_popcountll(__builtin_amdgcn_ballot_w64(same)) >=
+           __builtin_popcountll(__builtin_amdgcn_ballot_w64(has));
+}
+
 // RREG: the masked slots take the lanes' aperture values from registers
 // (else from the LDS copy, which costs fewer registers).
 // TT: traveltime kind (TT_TABLE: one-way time table, W = 1; TT_LTABLE: one
@@ -499,8 +511,13 @@ __device__ __forceinline__ Pair pair_table_ext(const Params& P, double ts, float
 // bounds, scale) (float4) [P.tb each], the aperture values [KS * 16], the tile box
 // [4 per wavefront], the candidates of two passes [2 x NW * 4], the
 // per-wavefront counts [2 x 16] and the list of near traces [P.list_cap].
-template <int NW, int CWQ, int KS, int TS, bool TF, int WK, bool RREG, int TT = TT_DSR, bool PX = false, int S16 = 0>
-__device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, int zc, float* lds) {
+// [lo, hi): the traces of bin b.  OWN (float32 table times): every pair reads both
+// its legs (no source leg is kept).
+template <int NW, int CWQ, int KS, int TS, bool TF, int WK, bool RREG, int TT = TT_DSR, bool PX = false, int S16 = 0,
+          bool OWN = false>
+__device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_t hi, int b, int tile, int zc,
+                                             float* lds) {
+    static_assert(!OWN || (is_table(TT) && !PX), "own legs: float32 table times");
     static_assert(!(PX && TT == TT_AA), "no extended-precision anti-alias kernels");
     // S16: the 16-bit storage type (BF16 or F16) staged as it is, 0 for float staging
     static_assert(!(S16 && (PX || TT == TT_AA)), "16-bit staging: float32 time, no anti-alias filter");
@@ -560,8 +577,6 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
 #pragma unroll
         for (int k = 0; k < KS; ++k) acc[q][k] = 0.0f;
 
-    int64_t lo, hi;
-    bin_range(P.bin, P.n_traces, b, lo, hi);
     const float tfo = P.tf_off;
     const double tfod = P.tf_off_d;
 
@@ -616,6 +631,23 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
     for (int k = 0; k < KS; ++k) mono_lane = mono_lane && (!(T.R[k] >= 0.0f) || T.B[k] >= 0.0f);
     const bool windows = TT == TT_DSR && __builtin_amdgcn_ballot_w64(!mono_lane) == 0;
     const int first_lo = TF ? -1 : 0;  // lowest staged sample (t_first = 0 gives u >= 0)
+
+    // Table times: the pairs of slots k and k + 1, of the trace whose row offset, bounds and scale are bd.
+    auto add_table_pairs = [&](const Pair& p0, const Pair& p1, const float4& bd, uint32_t full, int k, float hm, int q) {
+        const int rb = __float_as_int(bd.x);
+        const float* row = sTr + rb;
+        const uint32_t* sw = reinterpret_cast<const uint32_t*>(sTr);
+        float a0, b0, a1, b1;
+        if (S16) {
+            widen_pair<S16>(read_pair16(sw, rb + p0.i), a0, b0);
+            widen_pair<S16>(read_pair16(sw, rb + p1.i), a1, b1);
+        } else {
+            a0 = row[p0.i], b0 = row[p0.i + 1];
+            a1 = row[p1.i], b1 = row[p1.i + 1];
+        }
+        mask_add2<W_COSCOS, KS, RREG>(T, sR, full, k, d, hm, fmaf(p0.f, b0 - a0, a0), fmaf(p1.f, b1 - a1, a1),
+                                      S16 ? p0.r * bd.w : p0.r, S16 ? p1.r * bd.w : p1.r, acc[q][k], acc[q][k + 1]);
+    };
 
     // The near traces (source and receiver within reach of the box) of the bin
     // are listed first, one thread per trace, and only those are examined
@@ -840,6 +872,38 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
                 // The receiver leg of trace t reaches the depth lanes through the LDS
                 // crossbar; the next live trace's is requested before trace t is evaluated.
                 const int row4 = 4 * (lane & ~(kGroup - 1));  // crossbar address of the lane's row
+                if constexpr (OWN) {
+                    for (; live; live &= live - 1) {
+                        const int tc = __builtin_ctz(live);
+                        const float hs2 = bperm_f(row4 | 4 * tc, Lp.hs2), hr2 = bperm_f(row4 | 4 * tc, Lp.hr2);
+                        const float4 bd = sBnd[t0 + tc];
+                        float hm;
+                        asm("v_max_f32 %0, %1, %2" : "=v"(hm) : "v"(hs2), "v"(hr2));
+                        uint32_t any, full;
+                        slot_masks<KS>(T, hm, any, full);
+                        if (!any) continue;
+                        const TLeg Ls = table_leg(P, hs2), Lr = table_leg(P, hr2);
+                        const int vs = 4 * ((LAT ? lc.off : 0) + Ls.off + z0 + d);
+                        const int vr = 4 * ((LAT ? lc.off : 0) + Lr.off + z0 + d);
+#pragma unroll
+                        for (int k = 0; k < KS; k += 2) {
+                            if ((any >> k) & 3u) {
+                                const int o0 = min(64 * k, vl), o1 = min(64 * k + 64, vl);
+                                float s0 = 1.0f, s1 = 1.0f;
+                                if (P.tamp) {
+                                    s0 = table_amp_at<LAT>(P, Ls.f, lc, vs + o0);
+                                    s1 = table_amp_at<LAT>(P, Ls.f, lc, vs + o1);
+                                }
+                                const TTime ts0 = LAT ? ltable_time_at(P, Ls.f, lc, vs + o0) : table_time_at(P, Ls.f, vs + o0);
+                                const TTime ts1 = LAT ? ltable_time_at(P, Ls.f, lc, vs + o1) : table_time_at(P, Ls.f, vs + o1);
+                                const Pair p0 = pair_table<TF, LAT>(P, ts0, s0, Lr.f, vr + o0, bd.y, bd.z, lc);
+                                const Pair p1 = pair_table<TF, LAT>(P, ts1, s1, Lr.f, vr + o1, bd.y, bd.z, lc);
+                                add_table_pairs(p0, p1, bd, full, k, hm, q);
+                            }
+                        }
+                    }
+                    continue;
+                }
                 int t = __builtin_ctz(live);
                 float hr2n = bperm_f(row4 | 4 * t, Lp.hr2);
                 double Hrn = 0.0;
@@ -902,24 +966,12 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int b, int tile, i
                     } else if constexpr (is_table(TT)) {
                         const TLeg Lr = table_leg(P, hr2);
                         const int vr = 4 * ((LAT ? lc.off : 0) + Lr.off + z0 + d);
-                        const float* row = sTr + rb;
-                        const uint32_t* sw = reinterpret_cast<const uint32_t*>(sTr);
 #pragma unroll
                         for (int k = 0; k < KS; k += 2) {
                             if ((any >> k) & 3u) {
                                 const Pair p0 = pair_table<TF, LAT>(P, TTime{S.base[k], S.inc[k]}, S.amp[k], Lr.f, vr + min(64 * k, vl), wlo, whi, lc);
                                 const Pair p1 = pair_table<TF, LAT>(P, TTime{S.base[k + 1], S.inc[k + 1]}, S.amp[k + 1], Lr.f, vr + min(64 * k + 64, vl), wlo, whi, lc);
-                                float a0, b0, a1, b1;
-                                if (S16) {
-                                    widen_pair<S16>(read_pair16(sw, rb + p0.i), a0, b0);
-                                    widen_pair<S16>(read_pair16(sw, rb + p1.i), a1, b1);
-                                } else {
-                                    a0 = row[p0.i], b0 = row[p0.i + 1];
-                                    a1 = row[p1.i], b1 = row[p1.i + 1];
-                                }
-                                mask_add2<W_COSCOS, KS, RREG>(T, sR, full, k, d, hm, fmaf(p0.f, b0 - a0, a0),
-                                                              fmaf(p1.f, b1 - a1, a1), S16 ? p0.r * scl : p0.r,
-                                                              S16 ? p1.r * scl : p1.r, acc[q][k], acc[q][k + 1]);
+                                add_table_pairs(p0, p1, bd, full, k, hm, q);
                             }
                         }
                     } else if constexpr (AA) {
@@ -1042,7 +1094,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(KS <= 8
 void migrate_kernel(Params P) {
     extern __shared__ __align__(16) float lds[];
     constexpr bool RREG = true;
-    migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16>(P, blockIdx.z, blockIdx.x, blockIdx.y, lds);
+    const int b = blockIdx.z, tile = blockIdx.x, zc = blockIdx.y;
+    int64_t lo, hi;
+    bin_range(P.bin, P.n_traces, b, lo, hi);
+    if constexpr (is_table(TT) && !PX) {
+        if (!sources_repeat(P, lo, hi)) {
+            migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16, true>(P, lo, hi, b, tile, zc, lds);
+            return;
+        }
+    }
+    migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16>(P, lo, hi, b, tile, zc, lds);
 }
 
 // Batched persistent form: work items (problem, bin, column tile, depth
@@ -1065,8 +1126,13 @@ void migrate_batch_kernel(const Params* __restrict__ probs,
         if (it >= n_items) break;
         const int4 w = items[it];  // (problem, bin, tile, zchunk)
         const Params P = probs[w.x];
-        if (w.z < 0) zero_tile<NW, CWQ, KS, TS>(P, w.y, -1 - w.z, w.w);
-        else migrate_tile<NW, CWQ, KS, TS, TF, WK, false, TT_DSR, PX>(P, w.y, w.z, w.w, lds);
+        if (w.z < 0) {
+            zero_tile<NW, CWQ, KS, TS>(P, w.y, -1 - w.z, w.w);
+        } else {
+            int64_t lo, hi;
+            bin_range(P.bin, P.n_traces, w.y, lo, hi);
+            migrate_tile<NW, CWQ, KS, TS, TF, WK, false, TT_DSR, PX>(P, lo, hi, w.y, w.z, w.w, lds);
+        }
     }
 }
 
