@@ -486,16 +486,38 @@ __device__ __forceinline__ Pair pair_table_ext(const Params& P, double ts, float
     return p;
 }
 
-// Whether at least half of the traces [lo, hi) have the source of the trace before
-// them, from 64 places among them (one wavefront; the same answer in all).
-__device__ __forceinline__ bool sources_repeat(const Params& P, int64_t lo, int64_t hi) {
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int64_t j = lo + (hi - lo) * lane / kLanes;
-    const bool has = j + 1 < hi;
-    bool same = false;
-    if (has) same = P.src[2 * j] == P.src[2 * j + 2] && P.src[2 * j + 1] == P.src[2 * j + 3];
-    return 2 * __builtin_popcountll(__builtin_amdgcn_ballot_w64(same)) >=
-           __builtin_popcountll(__builtin_amdgcn_ballot_w64(has));
+// Kernels that have a second form, for traces whose sources do not repeat (OWN): there
+// a kept leg costs more than it saves, as it is formed for every slot, its reads are
+// waited for before the receiver's are asked for, and it holds registers.  ms, random
+// trace order, kept / own legs / before legs were kept (square-root times, extended
+// ones, tables): 10 000 traces -> 16 x 103 x 97 x 107 1.84 / 1.62 / 1.78, 2.89 / 2.28
+// / 2.47, 3.74 / 3.07 / 3.05; 36 864 -> 10 x 90 x 80 x 300 25.9 / 22.4 / 28.3, 46.9 /
+// 40.4 / 48.7, 52.7 / 43.3 / 50.6.  Not for the extended tables and the anti-alias
+// filter, nor for shapes with trace parts, which gain little (59 against 57 us on
+// 1536 traces) and whose short calls would wait for the sample (58.1 -> 59.8 us).
+constexpr bool own_legs(int tt, bool px, int ts) { return ts == 1 && (tt == TT_DSR || (is_table(tt) && !px)); }
+
+// Whether at least half of the traces have the source of the trace before them, from
+// 64 places among them (one wavefront; the same answer in all): the reads, made ahead
+// of the bin's, and the answer.
+struct SourceSample {
+    float x0, y0, x1, y1;
+    bool has;
+};
+__device__ __forceinline__ SourceSample sample_sources(const Params& P) {
+    const int64_t j = P.n_traces * (threadIdx.x & (kLanes - 1)) / kLanes;
+    SourceSample s{0.0f, 0.0f, 0.0f, 0.0f, j + 1 < P.n_traces};
+    if (s.has) {
+        s.x0 = P.src[2 * j];
+        s.y0 = P.src[2 * j + 1];
+        s.x1 = P.src[2 * j + 2];
+        s.y1 = P.src[2 * j + 3];
+    }
+    return s;
+}
+__device__ __forceinline__ bool sources_repeat(const SourceSample& s) {
+    const uint64_t same = __builtin_amdgcn_ballot_w64(s.has && s.x0 == s.x1 && s.y0 == s.y1);
+    return 2 * __builtin_popcountll(same) >= __builtin_popcountll(__builtin_amdgcn_ballot_w64(s.has));
 }
 
 // RREG: the masked slots take the lanes' aperture values from registers
@@ -511,13 +533,12 @@ __device__ __forceinline__ bool sources_repeat(const Params& P, int64_t lo, int6
 // bounds, scale) (float4) [P.tb each], the aperture values [KS * 16], the tile box
 // [4 per wavefront], the candidates of two passes [2 x NW * 4], the
 // per-wavefront counts [2 x 16] and the list of near traces [P.list_cap].
-// [lo, hi): the traces of bin b.  OWN (float32 table times): every pair reads both
-// its legs (no source leg is kept).
+// [lo, hi): the traces of bin b.  OWN: no source leg is kept, every pair forms both.
 template <int NW, int CWQ, int KS, int TS, bool TF, int WK, bool RREG, int TT = TT_DSR, bool PX = false, int S16 = 0,
           bool OWN = false>
 __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_t hi, int b, int tile, int zc,
                                              float* lds) {
-    static_assert(!OWN || (is_table(TT) && !PX), "own legs: float32 table times");
+    static_assert(!OWN || own_legs(TT, PX, TS), "no such form");
     static_assert(!(PX && TT == TT_AA), "no extended-precision anti-alias kernels");
     // S16: the 16-bit storage type (BF16 or F16) staged as it is, 0 for float staging
     static_assert(!(S16 && (PX || TT == TT_AA)), "16-bit staging: float32 time, no anti-alias filter");
@@ -647,6 +668,27 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_
         }
         mask_add2<W_COSCOS, KS, RREG>(T, sR, full, k, d, hm, fmaf(p0.f, b0 - a0, a0), fmaf(p1.f, b1 - a1, a1),
                                       S16 ? p0.r * bd.w : p0.r, S16 ? p1.r * bd.w : p1.r, acc[q][k], acc[q][k + 1]);
+    };
+
+    // Square-root times: slots k and k + 1, (a, s) their source legs and roots.
+    auto add_root_pairs = [&](float a0, float s0, float a1, float s1, float hr2, const float4& bd, uint32_t full,
+                              int k, float hm, int q) {
+        const int rb = __float_as_int(bd.x);
+        float v0, v1, r0, r1;
+        if (S16) {
+            mig_pair16<TF, WK, S16>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], a0, s0, a1, s1, hr2,
+                                    reinterpret_cast<const uint32_t*>(sTr) + rb, bd.w, tfo, bd.y, bd.z, v0, v1, r0, r1);
+        } else {
+            mig_pair<TF, WK>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], a0, s0, a1, s1, hr2,
+                             reinterpret_cast<const float2*>(sTr) + rb, tfo, bd.y, bd.z, v0, v1, r0, r1);
+        }
+        mask_add2<S16 ? W_COSCOS : WK, KS, RREG>(T, sR, full, k, d, hm, v0, v1, r0, r1, acc[q][k], acc[q][k + 1]);
+    };
+    // Extended square-root times: slot k, (t, s) its source leg's time and seed.
+    auto add_ext_slot = [&](double t, float s, double Hr, const float4& bd, int k, float hm, int q) {
+        const float R = RREG ? T.R[k] : sR[k * kGroup + d];
+        mig_slot_ext<TF, WK>(T.A[k], T.B[k], t, s, Hr, hm, reinterpret_cast<const float2*>(sTr) + __float_as_int(bd.x),
+                             P.inv_dt, tfod, static_cast<int>(bd.y), static_cast<int>(bd.z), bd.y, bd.z, R, acc[q][k]);
     };
 
     // The near traces (source and receiver within reach of the box) of the bin
@@ -873,21 +915,46 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_
                 // crossbar; the next live trace's is requested before trace t is evaluated.
                 const int row4 = 4 * (lane & ~(kGroup - 1));  // crossbar address of the lane's row
                 if constexpr (OWN) {
-                    for (; live; live &= live - 1) {
-                        const int tc = __builtin_ctz(live);
-                        const float hs2 = bperm_f(row4 | 4 * tc, Lp.hs2), hr2 = bperm_f(row4 | 4 * tc, Lp.hr2);
+                    // both legs of every pair; the next live trace's lengths are requested before
+                    // trace tc is evaluated
+                    int t = __builtin_ctz(live);
+                    float hs2n = bperm_f(row4 | 4 * t, Lp.hs2), hr2n = bperm_f(row4 | 4 * t, Lp.hr2);
+                    double Hsn = 0.0, Hrn = 0.0;
+                    if (PX) {
+                        Hsn = bperm_d(row4 | 4 * t, Lx.hs2);
+                        Hrn = bperm_d(row4 | 4 * t, Lx.hr2);
+                    }
+                    for (;;) {
+                        const int tc = t;
+                        const float hs2 = hs2n, hr2 = hr2n;
+                        const double Hs = Hsn, Hr = Hrn;
                         const float4 bd = sBnd[t0 + tc];
+                        live ^= 1u << tc;
+                        const bool more = live != 0;
+                        if (more) {
+                            t = __builtin_ctz(live);
+                            hs2n = bperm_f(row4 | 4 * t, Lp.hs2);
+                            hr2n = bperm_f(row4 | 4 * t, Lp.hr2);
+                            if (PX) {
+                                Hsn = bperm_d(row4 | 4 * t, Lx.hs2);
+                                Hrn = bperm_d(row4 | 4 * t, Lx.hr2);
+                            }
+                        }
                         float hm;
                         asm("v_max_f32 %0, %1, %2" : "=v"(hm) : "v"(hs2), "v"(hr2));
                         uint32_t any, full;
                         slot_masks<KS>(T, hm, any, full);
-                        if (!any) continue;
-                        const TLeg Ls = table_leg(P, hs2), Lr = table_leg(P, hr2);
-                        const int vs = 4 * ((LAT ? lc.off : 0) + Ls.off + z0 + d);
-                        const int vr = 4 * ((LAT ? lc.off : 0) + Lr.off + z0 + d);
+                        if (!any) {
+                            if (!more) break;
+                            continue;
+                        }
+                        if constexpr (is_table(TT)) {
+                            const TLeg Ls = table_leg(P, hs2), Lr = table_leg(P, hr2);
+                            const int vs = 4 * ((LAT ? lc.off : 0) + Ls.off + z0 + d);
+                            const int vr = 4 * ((LAT ? lc.off : 0) + Lr.off + z0 + d);
 #pragma unroll
-                        for (int k = 0; k < KS; k += 2) {
-                            if ((any >> k) & 3u) {
+                            for (int k = 0; k < KS; k += 2) {
+                                if (!((any >> k) & 3u)) continue;
                                 const int o0 = min(64 * k, vl), o1 = min(64 * k + 64, vl);
                                 float s0 = 1.0f, s1 = 1.0f;
                                 if (P.tamp) {
@@ -900,7 +967,25 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_
                                 const Pair p1 = pair_table<TF, LAT>(P, ts1, s1, Lr.f, vr + o1, bd.y, bd.z, lc);
                                 add_table_pairs(p0, p1, bd, full, k, hm, q);
                             }
+                        } else if constexpr (PX) {
+#pragma unroll
+                            for (int k = 0; k < KS; ++k) {
+                                if (!((any >> k) & 1u)) continue;
+                                float A = T.A[k], B = T.B[k];
+                                asm volatile("" : "+v"(A), "+v"(B));  // as in mig_slot_ext
+                                const LegTimeX l = leg_time_ext(A, B, Hs);
+                                add_ext_slot(l.t, l.q, Hr, bd, k, hm, q);
+                            }
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < KS; k += 2) {
+                                if (!((any >> k) & 3u)) continue;
+                                const float a0 = fmaf(T.B[k], hs2, T.A[k]), a1 = fmaf(T.B[k + 1], hs2, T.A[k + 1]);
+                                add_root_pairs(a0, __builtin_amdgcn_sqrtf(a0), a1, __builtin_amdgcn_sqrtf(a1), hr2, bd,
+                                               full, k, hm, q);
+                            }
                         }
+                        if (!more) break;
                     }
                     continue;
                 }
@@ -988,37 +1073,14 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_
                             }
                         }
                     } else if constexpr (PX) {
-                        const int ilo = static_cast<int>(wlo), ihi = static_cast<int>(whi);
-                        const double wlod = wlo, whid = whi;
-                        const float2* row = reinterpret_cast<const float2*>(sTr) + rb;
 #pragma unroll
-                        for (int k = 0; k < KS; ++k) {
-                            if ((any >> k) & 1u) {
-                                const float R = RREG ? T.R[k] : sR[k * kGroup + d];
-                                mig_slot_ext<TF, WK>(T.A[k], T.B[k], S.t[k], S.q[k], Hr, hm, row, P.inv_dt, tfod, ilo,
-                                                     ihi, wlod, whid, R, acc[q][k]);
-                            }
-                        }
+                        for (int k = 0; k < KS; ++k)
+                            if ((any >> k) & 1u) add_ext_slot(S.t[k], S.q[k], Hr, bd, k, hm, q);
                     } else {
 #pragma unroll
-                        for (int k = 0; k < KS; k += 2) {
-                            if ((any >> k) & 3u) {
-                                float v0, v1, r0, r1;
-                                if (S16) {
-                                    mig_pair16<TF, WK, S16>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], S.a[k], S.s[k],
-                                                            S.a[k + 1], S.s[k + 1], hr2,
-                                                            reinterpret_cast<const uint32_t*>(sTr) + rb, scl, tfo, wlo,
-                                                            whi, v0, v1, r0, r1);
-                                } else {
-                                    mig_pair<TF, WK>(T.A[k], T.B[k], T.A[k + 1], T.B[k + 1], S.a[k], S.s[k],
-                                                     S.a[k + 1], S.s[k + 1], hr2,
-                                                     reinterpret_cast<const float2*>(sTr) + rb, tfo, wlo, whi, v0, v1,
-                                                     r0, r1);
-                                }
-                                mask_add2<S16 ? W_COSCOS : WK, KS, RREG>(T, sR, full, k, d, hm, v0, v1, r0, r1,
-                                                                         acc[q][k], acc[q][k + 1]);
-                            }
-                        }
+                        for (int k = 0; k < KS; k += 2)
+                            if ((any >> k) & 3u)
+                                add_root_pairs(S.a[k], S.s[k], S.a[k + 1], S.s[k + 1], hr2, bd, full, k, hm, q);
                     }
                     if (!more) break;
                 }
@@ -1060,6 +1122,23 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_
     }
 }
 
+// Bin b, column tile, depth chunk of a problem: the form its order of traces asks for.
+template <int NW, int CWQ, int KS, int TS, bool TF, int WK, bool RREG, int TT = TT_DSR, bool PX = false, int S16 = 0>
+__device__ __forceinline__ void migrate_item(const Params& P, int b, int tile, int zc, float* lds) {
+    int64_t lo, hi;
+    if constexpr (own_legs(TT, PX, TS)) {
+        const SourceSample sample = sample_sources(P);
+        bin_range(P.bin, P.n_traces, b, lo, hi);
+        if (!sources_repeat(sample)) {
+            migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16, true>(P, lo, hi, b, tile, zc, lds);
+            return;
+        }
+    } else {
+        bin_range(P.bin, P.n_traces, b, lo, hi);
+    }
+    migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16>(P, lo, hi, b, tile, zc, lds);
+}
+
 // Store zeros into a tile whose (column, trace) pairs are all outside the
 // aperture (known from the counting kernel): its image values are exactly 0.
 template <int NW, int CWQ, int KS, int TS>
@@ -1094,16 +1173,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(KS <= 8
 void migrate_kernel(Params P) {
     extern __shared__ __align__(16) float lds[];
     constexpr bool RREG = true;
-    const int b = blockIdx.z, tile = blockIdx.x, zc = blockIdx.y;
-    int64_t lo, hi;
-    bin_range(P.bin, P.n_traces, b, lo, hi);
-    if constexpr (is_table(TT) && !PX) {
-        if (!sources_repeat(P, lo, hi)) {
-            migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16, true>(P, lo, hi, b, tile, zc, lds);
-            return;
-        }
-    }
-    migrate_tile<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16>(P, lo, hi, b, tile, zc, lds);
+    migrate_item<NW, CWQ, KS, TS, TF, WK, RREG, TT, PX, S16>(P, blockIdx.z, blockIdx.x, blockIdx.y, lds);
 }
 
 // Batched persistent form: work items (problem, bin, column tile, depth
@@ -1126,13 +1196,8 @@ void migrate_batch_kernel(const Params* __restrict__ probs,
         if (it >= n_items) break;
         const int4 w = items[it];  // (problem, bin, tile, zchunk)
         const Params P = probs[w.x];
-        if (w.z < 0) {
-            zero_tile<NW, CWQ, KS, TS>(P, w.y, -1 - w.z, w.w);
-        } else {
-            int64_t lo, hi;
-            bin_range(P.bin, P.n_traces, w.y, lo, hi);
-            migrate_tile<NW, CWQ, KS, TS, TF, WK, false, TT_DSR, PX>(P, lo, hi, w.y, w.z, w.w, lds);
-        }
+        if (w.z < 0) zero_tile<NW, CWQ, KS, TS>(P, w.y, -1 - w.z, w.w);
+        else migrate_item<NW, CWQ, KS, TS, TF, WK, false, TT_DSR, PX>(P, w.y, w.z, w.w, lds);
     }
 }
 

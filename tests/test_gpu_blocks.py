@@ -305,3 +305,29 @@ def test_batches_of_the_longest_records(ops, n_t):
         b.close()
         ref = ops.migrate(dp, tile=tile)
         assert bool(torch.equal(img, ref)) and bool(torch.any(img)), tile
+
+
+# Traces whose sources repeat (a kept source leg) or do not (both legs of every pair), and a list
+# where half do: the same bits on every tile without trace parts, 16-bit staging included, all
+# within the parity bar of the oracle.
+@pytest.mark.parametrize("run", [1, 2, 5])
+@pytest.mark.parametrize("kind", ["fp32", "extended", "table", "ltable"])
+@pytest.mark.parametrize("dtype,t_first", [("f32", 0.1), ("bf16", 0.0), ("f16", 0.1)])
+def test_repeated_and_single_sources(ops, oracle_lib, run, kind, dtype, t_first):
+    p = shot_order(survey.make_random(run + 3, 130, 300, 21, 3, 75, 3, t_first=t_first, spread=200.0), run)
+    if kind == "table":
+        p = survey.with_curved_ray_table(p, 10.0, amplitude=True)
+    elif kind == "ltable":
+        p = survey.with_lateral_tables(p, lambda x, y: 1500.0 + 0.05 * x, 0.5, 600.0, 1500.0, 400.0, 400.0, 4, 4, dh=20.0)
+    dp = ops.to_device(p, dtype=dtype, prec="extended" if kind == "extended" else "fp32")
+    if dtype != "f32":
+        p = dataclasses.replace(p, data=survey.quantise(p.data, dtype)[2])
+    ref = oracle_lib.migrate(p)
+    assert np.any(ref)
+    first = ops.migrate(dp, tile=0)
+    for tile in range(ops.tile_count(0)):
+        img = ops.migrate(dp, tile=tile)
+        assert rel_l2(img.cpu().numpy(), ref) <= 1e-5, tile
+        assert tile >= 7 or bool(torch.equal(img, first)), tile
+        if dtype != "f32" and kind != "extended":
+            assert rel_l2(ops.migrate(dp, tile=tile + 256).cpu().numpy(), ref) <= 1e-5, tile
