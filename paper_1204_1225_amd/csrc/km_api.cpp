@@ -440,54 +440,77 @@ int64_t migrate_workgroups(int shape, const km_grid& g) {
 // and examines a trace once for many columns; a small image needs small tiles
 // to fill 256 CUs, and the smallest ones several wavefronts on the same columns
 // with the traces dealt out among them (trace_parts; one workgroup per CU is
-// enough for those, so they take level 3: twice the LDS, larger blocks).  Each
-// line is where the two sides ran alike.  Square-root times: 3000 workgroups of
-// tile 5 ran 14.6 ms against 14.8 ms with tile 6, 576 of them 1.97 against 1.64
-// ms; 512 of tile 6 ran 0.064 ms against 0.074 ms with tile 7, 256 of them 0.61
-// against 0.29 ms; 256 of tile 7 ran 0.29 ms against 0.38 ms with tile 8, 128 of
-// them 0.090 against 0.065 ms.  Tables and the anti-alias filter stage more per
-// trace, so tile 6 (16 columns) never pays: 512 workgroups of tile 5 ran 4.37 ms
-// against 6.6 ms with tile 6 and 5.4 ms with tile 7 (table), 8.1 against 11.4
-// and 9.1 ms (anti-alias); 480 of them 6.9 ms against 5.5 ms with tile 7
-// (lateral tables).
+// enough for those, so they take level 3: twice the LDS, larger blocks).  The lines
+// lie where the tiles on their two sides take the same time on average over lines
+// and areal images; single images of one size lie up to 20 % to either side.  ms
+// with tiles 5 / 6 / 7, by workgroups of tile 5:
+//   square-root times  792 0.70 / 0.58 / 0.82    1320 2.66 / 2.30 / 3.04    1800
+//                      0.506 / 0.501 / 0.92    2512 1.86 / 2.08 / 3.57
+//   extended times     1290 3.52 / 2.95 / 4.14    2106 1.68 / 1.43 / 2.43    3792
+//                      2.38 / 2.42 / 3.80
+//   anti-alias filter  544 2.08 / 2.17 / 1.68    700 1.77 / 1.83 / 1.91    896 1.92 /
+//                      2.48 / 2.95
+//   tables             608 7.39 / 7.35 / 5.85    780 4.96 / 5.27 / 5.14    880 0.79 /
+//                      0.76 / 0.78    1274 0.87 / 1.23 / 1.32
+//   lateral tables     480 9.26 / 8.60 / 6.90    696 7.01 / 5.84 / 8.40    1224 54.9 /
+//                      47.0 / 53.0    2352 40.8 / 45.6 / 50.4
+// Below, 256 workgroups of tile 7 ran 0.29 ms against 0.38 ms with tile 8, 128 of them
+// 0.090 against 0.065 ms (square-root times).
 // Tile 2 (128 columns) with invariant tables from 8192 workgroups, where staging whole
 // records outweighs the finer tile (2.54 s against 2.86 s on 65 536 workgroups, 188
 // against 190 ms on 16 384; 163 against 158 ms on 32 768 shallower ones), and where the
-// grid of tile 5 would pass 2^32 threads.  Depths that need more than kMaxChunks
+// grid of tile 5 would pass 2^31 threads.  Depths that need more than kMaxChunks
 // chunks of 128 take chunks of 256 with laterally varying tables.
 template <typename Workgroups>
-int default_migrate_tile(int kind, int nz, Workgroups workgroups) {
+int default_migrate_tile(int kind, int prec, int nz, Workgroups workgroups) {
     if (kind == KIND_LTABLE && nz > 128 * kMaxChunks) return 3;
     const int64_t wide = workgroups(5);  // 64 columns x 128 depths
     if (wide >= int64_t{1} << 22 || (kind == KIND_TABLE && wide >= 8192)) return 2;
-    if (wide >= (kind == KIND_DSR ? 1024 : 512)) return 5;
+    const int64_t line = kind == KIND_DSR      ? (prec == KM_TIME_EXTENDED ? 3600 : 1800)
+                         : kind == KIND_LTABLE ? 2400
+                         : kind == KIND_TABLE  ? 800
+                                               : 640;
+    if (wide >= line) return 5;
     const int64_t n = workgroups(6);     // 16 columns x 128 depths, also of shape 7
     if (kind == KIND_DSR && n >= 400) return 6;
+    if (kind == KIND_LTABLE && wide >= 640) return 6;
     return (n >= 192 ? 7 : 8) + 3 * kTileLevelStride;  // 4 parts on 16 columns x 128 or 64 depths
 }
 
 // Untuned choice for the adjoint: 8 waves x 4 slots x 1 trace quad, with 16
 // waves where there are no more quads than CUs (0.117 ms against 0.151 ms on 225
-// quads).  With table traveltimes 16 waves x 8 slots x 3 quads, and 8 waves x 8
-// slots x 3 quads with laterally varying tables: their gathers favour more traces
-// per workgroup (350 ms against 369 ms and 223 ms against 227 ms on 50 000
-// traces), once those workgroups fill the chip.  Below, fewer quads: 31.0 ms
-// against 32.4 ms with 2 on 18 000 traces (table), 0.20 ms against 0.25 ms with 1 on
-// 1800; lateral 6.9 ms against 8.4 ms with 1 on 8000, extended times
-// 1.8 ms against 5.0 ms on 4096.
+// quads).  With many traces table times take 16 waves x 8 slots x 3 quads, and
+// 8 waves x 8 slots x 3 quads with laterally varying tables: their gathers favour
+// more traces per workgroup.  Below, one quad: its columns are fewer and its
+// workgroups more.  ms with one quad / the many-trace shape, traces in shot order:
+// table 1.48 / 2.11 (12 100), 0.82 / 1.49 (14 400 on a smaller image), 22.4 / 26.4
+// (23 409), 65.2 / 65.9 (24 336), 28.7 / 30.9 (76 176); lateral, float32 14.5 / 16.2
+// (23 104), 35.5 / 35.6 (32 340), 120 / 120 (166 000); lateral, extended (16 waves) 3.4
+// / 5.4 (15 876), 122 / 122 (18 496), 220 / 205 (24 336).  Traces in random order span
+// more columns, which 12 of them share: 29.2 / 25.9 ms (table, 19 600), 165 / 144 ms
+// (lateral, 16 900); the lines are therefore drawn below the points of equal time of
+// shot order.
+// Few traces with float32 square-root times fill the chip better with 8 slots (0.262
+// against 0.307 ms with 2040 traces, 0.245 against 0.269 ms with 2500; 0.109 against
+// 0.114 ms with 4452; 1.13 against 1.12 ms with 5184).
 // Records whose quad of float64 rows lets only two workgroups share a CU take 8
 // slots (0.43 ms against 0.45 ms on 2400 samples; three workgroups of 1600
-// samples 0.40 ms with 4 slots against 0.42 ms), and where one fills it, 16 waves (0.49
-// ms against 0.65 ms on 3000 samples; extended times, 4 slots: 0.69 ms against 0.77 ms).
+// samples 0.40 ms with 4 slots against 0.42 ms), unless one chunk of 8 slots would
+// hold few depths (0.26 ms with 4 slots, 0.36 ms with 8 on 69 depths), and where one
+// fills it, 16 waves (0.49 ms against 0.65 ms on 3000 samples; extended times, 4 slots:
+// 0.69 ms against 0.77 ms).
 // Depths that need more than kMaxChunks chunks of 4 slots take 8 slots with tables.
 int default_demigrate_tile(int kind, int prec, int nz, int64_t n_traces, int64_t quad_bytes) {
     if (nz > 64 * kMaxChunks && (kind == KIND_TABLE || kind == KIND_LTABLE)) return kind == KIND_TABLE ? 1 : 4;
     const bool fp32 = prec != KM_TIME_EXTENDED;
     const bool alone = 2 * quad_bytes > kMaxLds;
     if (n_traces <= 4 * 256) return 5;
-    if (kind == KIND_LTABLE) return n_traces >= 12 * 2048 ? 4 : alone ? 2 : fp32 ? 3 : 0;
-    if (kind == KIND_TABLE) return n_traces >= 12 * 1536 ? 1 : n_traces >= 12 * 256 || alone ? 2 : 3;
-    if (kind == KIND_DSR && fp32) return alone ? 2 : 3 * quad_bytes > kMaxLds ? 0 : 3;
+    if (kind == KIND_LTABLE) return n_traces >= (fp32 ? 24576 : 18432) ? 4 : !fp32 ? 5 : alone ? 2 : 3;
+    if (kind == KIND_TABLE) return n_traces >= 18432 || (n_traces >= 3072 && nz >= 160) ? 1 : alone ? 2 : 3;
+    if (kind == KIND_DSR && fp32) {
+        const bool two = 3 * quad_bytes > kMaxLds;
+        return alone ? 2 : n_traces < 4608 || (two && nz > 96) ? 0 : 3;
+    }
     return alone ? 5 : 3;
 }
 
@@ -610,7 +633,7 @@ km_status migrate_impl(const km_traces* traces, const km_grid* grid, const km_tr
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
     st = pick_tile(0, tile, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples, image_columns(*grid),
-                   [&] { return default_migrate_tile(kind, grid->nz, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
+                   [&] { return default_migrate_tile(kind, tt->time_precision, grid->nz, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
                    &shape);
     if (st != KM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1118,7 +1141,7 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
     };
     const auto fits = [&](int t) { return workgroups(t % kTileLevelStride) <= max_items; };
     const auto untuned = [&] {
-        const int t = default_migrate_tile(KIND_DSR, max_nz, workgroups);
+        const int t = default_migrate_tile(KIND_DSR, probs[0].tt.time_precision, max_nz, workgroups);
         return fits(t) ? t : 2;
     };
     km_status st = pick_tile(0, tile, probs[0].traces.dtype, KIND_DSR, probs[0].tt.time_precision, max_nz, max_nt,
