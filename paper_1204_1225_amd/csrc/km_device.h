@@ -840,7 +840,6 @@ template <int KS>
 struct ChunkTables {
     float A[KS], B[KS], R[KS];
     float rlo, rhi, rmax;
-    uint32_t clean;  // bit k: every lane of slot k is valid (wavefront-uniform)
 };
 
 // E (given with CUT): no aperture value beyond record_aperture's.
@@ -850,7 +849,7 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int z
     const int lane = threadIdx.x & (kLanes - 1);
     float rmax = -1.0f;
     float rlo_mine = __builtin_inff(), rhi_mine = -__builtin_inff();
-    uint32_t clean = 0;
+    uint64_t past = 0;
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
         const int iz = slot_depth<IL>(z0, k, d);
@@ -875,15 +874,11 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int z
         float R = valid ? r2 : -1.0f;
         // only where the longest legs' time may pass the record's end (bounding every
         // slot cost small images 6 %)
-        if (CUT && __builtin_amdgcn_ballot_w64(valid && !(4.0f * fmaf(B, R, A) <= E.end * E.end))) {
-            const float cut = record_aperture(A, B, E);
-            R = cut < R ? cut : R;  // a NaN aperture stays one: it admits no pair
-        }
+        if (CUT) past |= __builtin_amdgcn_ballot_w64(valid && !(4.0f * fmaf(B, R, A) <= E.end * E.end));
         T.A[k] = A;
         T.B[k] = B;
         T.R[k] = R;
         if (sR && lane < kGroup) sR[k * kGroup + d] = R;
-        if ((__builtin_amdgcn_ballot_w64(valid) & 0xFFFFull) == 0xFFFFull) clean |= 1u << k;
         // min / max over the 16 lanes of the group (all groups hold the same depths)
         // (a valid lane whose aperture is NaN or negative admits nothing: its slot is never full)
         float lo = valid ? fmaxf(R, -1.0f) : __builtin_inff();
@@ -896,9 +891,20 @@ __device__ __forceinline__ void load_chunk_tables(const Params& P, int z0, int z
         }
         rmax = fmaxf(rmax, hi);
     }
+    if (CUT && past) {
+        rmax = -1.0f;
+        rhi_mine = -__builtin_inff();
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const float cut = record_aperture(T.A[k], T.B[k], E);
+            if (cut < T.R[k]) T.R[k] = cut;  // a NaN aperture stays one: it admits no pair
+            const float hi = group_max(T.R[k]);
+            if (d == k) rhi_mine = hi;
+            rmax = fmaxf(rmax, hi);
+        }
+    }
     T.rlo = rlo_mine;
     T.rhi = rhi_mine;
-    T.clean = clean;
     // equal in every lane: make them scalar so that branches on them are uniform
     T.rmax = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(rmax)));
 }
