@@ -10,7 +10,7 @@
 //
 // Each trace is staged in LDS between zeros by one wavefront (a workgroup
 // filters kFirWaves traces at a time), or by the whole workgroup where the
-// record is long; it is fully staged before any of its output is written, so
+// traces are few or long; it is fully staged before any of its output is written, so
 // the output may be the input.  A lane produces kOut consecutive outputs from a
 // window of input values in registers: 4 taps cost one 16-byte read of the
 // trace and one broadcast 16-byte read of the taps for 4 kOut FMAs, each output
@@ -142,8 +142,12 @@ size_t fir_lds_bytes(int n, int K) {
 
 hipError_t launch_fir(const float* in, int64_t in_stride, float* out, int64_t out_stride, int64_t n_traces, int n,
                       const float* taps, int K, int c, int adjoint, hipStream_t s) {
-    // a wavefront per trace as long as three workgroups share a CU's LDS
-    const int per = fir_bytes(n, K, kFirWaves) <= 52 * 1024 ? kFirWaves : 1;
+    // A wavefront per trace where there are traces enough to fill the chip so, and as long as
+    // four workgroups share a CU's LDS; else a workgroup per trace.  us, the one / the other:
+    // 256 x 1500 samples, 65 taps 9.5 / 8.2; 256 x 600, 129 taps 10.5 / 8.2; 2000 x 600 11.1 /
+    // 11.3; 6000 x 1500 25.5 / 24.3; 20 000 x 1500 70 / 74; 256 and 20 000 x 3000, 129 taps
+    // 26.9 / 11.2 and 263 / 231.
+    const int per = n_traces >= 4096 && fir_bytes(n, K, kFirWaves) <= 40 * 1024 ? kFirWaves : 1;
     const int64_t blocks = std::min<int64_t>((n_traces + per - 1) / per, 256 * 16);
     const bool tight = fir_bytes(n, K, per) > 160 * 1024;
     return launch_with_lds(tight ? fir_kernel<true> : fir_kernel<false>, dim3(static_cast<unsigned>(blocks)),

@@ -331,3 +331,17 @@ def test_repeated_and_single_sources(ops, oracle_lib, run, kind, dtype, t_first)
         assert tile >= 7 or bool(torch.equal(img, first)), tile
         if dtype != "f32" and kind != "extended":
             assert rel_l2(ops.migrate(dp, tile=tile + 256).cpu().numpy(), ref) <= 1e-5, tile
+
+
+# From 4096 traces on a wavefront takes a trace, below a workgroup: the same sums.
+@pytest.mark.parametrize("n_t,K", [(70, 9), (601, 65)])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_filter_of_few_and_many_traces(ops, n_t, K, adjoint):
+    rng = np.random.default_rng(K)
+    x = rng.standard_normal((4097, n_t)).astype(np.float32)
+    h = rng.standard_normal(K).astype(np.float32)
+    ref = (oracle_filter.adjoint if adjoint else oracle_filter.forward)(x, h, K // 3)
+    t, taps = torch.from_numpy(x).cuda(), torch.from_numpy(h).cuda()
+    many = ops.trace_filter(t, taps, K // 3, adjoint=adjoint)
+    assert np.abs(many.cpu().numpy() - ref).max() <= 1e-6 * float(np.abs(h).sum()) * float(np.abs(x).max())
+    assert torch.equal(ops.trace_filter(t[:4095], taps, K // 3, adjoint=adjoint), many[:4095])
