@@ -3,9 +3,10 @@
 KirchhoffDemigrate: forward = demigration L (image -> traces, Kirchhoff
 modelling), backward = migration L^T (the transpose of Eq. (1)'s
 discretisation), so gradients of data-space losses flow to the image.
-KirchhoffMigrate is the mirror pair.  Both kernels evaluate every
-(trace, image point) pair identically, so each backward is the exact
-adjoint of its forward up to float32 summation rounding.
+KirchhoffMigrate is the mirror pair.  Both kernels give every (trace, image
+point) pair the same time and weight (bit for bit with float32 times, to the
+last float64 bits with extended ones), so each backward is the adjoint of its
+forward up to float32 rounding of the taps and the sums.
 """
 from __future__ import annotations
 

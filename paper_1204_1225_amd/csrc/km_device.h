@@ -166,36 +166,22 @@ __device__ __forceinline__ Legs legs(float px, float py, float4 sr) {
     return L;
 }
 
-// One (trace, image point) pair in sample units:
+// One (trace, image point) pair in sample units, float32 square-root times:
 //   a_s = A + B hs2, a_r = A + B hr2 (A = t0sq / dt^2, B = s2 / dt^2),
 //   w   = sqrt(a_s) + sqrt(a_r) [+ tf_off when t_first != 0], clamped to
 //         [wlo, whi]; the staged-row index of sample floor(u) is floor(w)
 //         (plus kLead through the row pointer when t_first == 0),
 //   i   = floor(w), f = w - i, and r = 1 / (a_s a_r) for the weight.
-// Migrate and demigrate both call this, so the transpose pair sees
-// bit-identical (i, f, r) for every pair.  CLAMP = false skips the clamp (for
-// callers that know every w lies in [wlo, whi]; the kernels all clamp).
+// Migrate (mig_pair) and demigrate (dem_merged) form a_s, a_r, w and r by the
+// same operations, so the transpose pair sees the same bits of them; 1 - f and
+// f are exact in one and rounded once as a product in the other.
 struct Pair {
     int32_t i;
     float f;
     float r;
 };
 
-template <bool TF, int WK, bool CLAMP = true>
-__device__ __forceinline__ Pair eval_pair(float A, float B, float hs2, float hr2, float tf_off, float wlo, float whi) {
-    const float as = fmaf(B, hs2, A);
-    const float ar = fmaf(B, hr2, A);
-    float w = __builtin_amdgcn_sqrtf(as) + __builtin_amdgcn_sqrtf(ar);
-    if (TF) w = w + tf_off;
-    if (CLAMP) w = __builtin_amdgcn_fmed3f(w, wlo, whi);
-    Pair p;
-    p.i = static_cast<int32_t>(w);
-    p.f = __builtin_amdgcn_fractf(w);
-    p.r = (WK == W_COSCOS) ? __builtin_amdgcn_rcpf(as * ar) : 1.0f;
-    return p;
-}
-
-// Extended-precision form of eval_pair (the PX kernels).  A float32 total
+// Its extended-precision form (the PX kernels).  A float32 total
 // time is rounded to 0.5 ulp of u (6e-5 samples at u = 1000, 1e-3 at 16000)
 // after the roundings of A, B, the two products and the two square roots, which
 // is a relative image error of about 1e-5 on data that change by O(1) between
@@ -211,7 +197,7 @@ __device__ __forceinline__ Pair eval_pair(float A, float B, float hs2, float hr2
 // with float32 precision.
 //   !TF: i = floor(w) clamped to [ilo, ihi] (the two row entries at a clamped
 //        index are zeros, or the pair is outside the aperture and masked);
-//   TF:  w clamped to [wlo, whi] first (as eval_pair; f = 0 at a bound).
+//   TF:  w clamped to [wlo, whi] first (f = 0 at a bound).
 // a = 0 exactly (W = 1 and t0 = 0 at zero offset) would give rsq = inf: the
 // tables replace A = 0 by kTinyA (a time of 3e-19 s).
 struct PairX {
@@ -284,7 +270,7 @@ __device__ __forceinline__ LegsX legs_ext(float px, float py, float4 sr) {
     return L;
 }
 
-// One pair with the anti-alias triangle filter (Params::aa_*).  As eval_pair
+// One pair with the anti-alias triangle filter (Params::aa_*): its float32 time
 // (clamped), plus the half-width p = |du/dx| dx + |du/dy| dy in samples,
 // du/dx = B ((x - x_s) / sqrt(a_s) + (x - x_r) / sqrt(a_r)) (likewise y),
 // clamped to [1, aa_max]; L = floor(p) and the blend weights
@@ -650,7 +636,7 @@ __device__ __forceinline__ PairX eval_pair_table_ext(const Params& P, TLegX Ls, 
     return p;
 }
 
-// The pair evaluation of eval_pair with table times (iz < nz); the clamp
+// A pair with table times (iz < nz); the clamp
 // bounds are those of clamp_bounds.  LAT: laterally varying tables at column
 // C.  r = A_s A_r with amplitude tables, else 1.
 template <bool TF, bool CLAMP = true, bool LAT = false>
@@ -669,7 +655,7 @@ __device__ __forceinline__ Pair eval_pair_table(const Params& P, TLeg Ls, TLeg L
     return p;
 }
 
-// Clamp bounds of eval_pair for a row of lt floats: reads at floor(w) and
+// Clamp bounds of a pair's time for a row of lt floats: reads at floor(w) and
 // floor(w) + 1 stay in [0, lt).  Without t_first the row pointer is advanced
 // by kLead and u >= 0 needs no lower clamp beyond 0.
 template <bool TF>

@@ -13,8 +13,8 @@
 // derives from ballots which 16-depth slots can hold a pair inside the aperture
 // and which are wholly inside, and evaluates those slots two at a time.  The
 // source leg's share of a pair is kept from trace to trace while the source
-// stays the same (SrcLeg); the receiver's costs one square root, the weight one
-// reciprocal, then the sample index and fraction, one 8-byte LDS read of the
+// stays the same (SrcLeg), unless the traces seldom share it (own_legs); the receiver's
+// costs one square root, the weight one reciprocal, then the sample index and fraction, one 8-byte LDS read of the
 // staged (sample, difference) pair, the interpolation and, at the aperture's
 // edge, the lane's mask.  Table times and the anti-alias filter use the same
 // blocks with their own staged forms (plain samples; float64 double running
@@ -278,8 +278,7 @@ template <int KS>
 struct SrcLeg<KS, TT_LTABLE, true> : SrcLeg<KS, TT_TABLE, true> {};
 
 // Two slots of one (column group, trace) pairing with square-root times.
-// (sa, ss): the source leg of each slot; hr2: the receiver leg.  FULL: every
-// lane of both slots is inside the aperture (wavefront-uniform).
+// (sa, ss): the source leg of each slot; hr2: the receiver leg.
 template <bool TF, int WK>
 __device__ __forceinline__ void mig_pair(float A0, float B0, float A1, float B1, float sa0, float ss0, float sa1,
                                          float ss1, float hr2, const float2* row, float tfo, float wlo, float whi,
@@ -555,7 +554,7 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_
     const int z0 = zc * P.zspan;
     const int z1 = min(z0 + P.zspan, P.nz);  // end of the chunk's depths
     const int nt = P.nt;
-    // staged-row index of sample k is k + koff (eval_pair adds kLead with t_first)
+    // staged-row index of sample k is k + koff (the time includes kLead with t_first)
     const int koff = TF ? kLead : 0;
     // staged form: (sample, difference) pairs for the square-root times (windows
     // of a few hundred samples), plain samples for the whole-record windows of
