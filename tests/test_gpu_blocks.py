@@ -345,3 +345,59 @@ def test_filter_of_few_and_many_traces(ops, n_t, K, adjoint):
     many = ops.trace_filter(t, taps, K // 3, adjoint=adjoint)
     assert np.abs(many.cpu().numpy() - ref).max() <= 1e-6 * float(np.abs(h).sum()) * float(np.abs(x).max())
     assert torch.equal(ops.trace_filter(t[:4095], taps, K // 3, adjoint=adjoint), many[:4095])
+
+
+# Adjoints of long records against the oracle, the pairs spread over the whole record (rows of
+# four, two and one workgroups per CU, and records of which fewer than four rows fit).  A float32
+# time is good to 3 x 2^-24 of itself, d samples at the record's end: each tap is off by at most d
+# of its weight, a relative L2 error of at most 2 d on taps that do not cancel; 4 d leaves room for
+# those that do.  A float32 table time has its leg length's rounding, 2^-24 of the part that grows
+# with it: within the same bound.  Extended times are good to 1e-9 samples: the parity bar.
+@pytest.mark.parametrize("n_t", [1500, 2530, 2560, 5090, 5110, 10300])
+@pytest.mark.parametrize("kind", ["fp32", "extended", "aa", "table"])
+def test_adjoint_of_long_records_against_the_oracle(ops, oracle_lib, n_t, kind):
+    p = survey.make_random(n_t, 13, n_t, 9, 2, 70, 2, weight=survey.WEIGHT_UNIT, dt=1.25 / n_t, dz=15.0, spread=50.0)
+    if kind == "aa":
+        p = dataclasses.replace(p, aa=(12.0, 12.0, 8))
+    elif kind == "table":
+        p = survey.with_curved_ray_table(p, 10.0)
+    m = survey.random_image(p, 3)
+    ref = oracle_lib.demigrate(p, m)
+    assert np.count_nonzero(ref) > 0.05 * ref.size and np.any(ref[:, -n_t // 10:]) and np.any(ref[:, :n_t // 5])
+    bar = 4 * 3 * 2.0 ** -24 * n_t if kind != "extended" else 1e-5
+    dp = ops.to_device(p, prec="extended" if kind == "extended" else "fp32")
+    for tile in [-1] + list(range(ops.tile_count(1))):
+        d = ops.demigrate(dp, torch.from_numpy(m).cuda(), tile=tile).cpu().numpy()
+        assert rel_l2(d, ref) <= bar, (tile, rel_l2(d, ref), bar)
+
+
+# One pair and records of one to three samples, its time 0.3 samples after the first: every lane,
+# slot and window edge of the kernels at its smallest.  The time is a few samples long before
+# t_first is taken off, good to 1e-6 samples in float32.
+@pytest.mark.parametrize("n_t", [1, 2, 3])
+@pytest.mark.parametrize("kind", ["fp32", "extended", "aa", "table"])
+@pytest.mark.parametrize("weight", [survey.WEIGHT_UNIT, survey.WEIGHT_COSCOS])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_single_pair(ops, oracle_lib, n_t, kind, weight, dtype):
+    p = survey.make_random(1, 1, n_t, 1, 1, 1, 1, weight=weight)
+    x = float(p.x[0])
+    src, rec = np.array([[x - 3.0, 0.0]], np.float32), np.array([[x + 4.0, 0.0]], np.float32)
+    T = sum(float(np.sqrt(p.t0sq[0] + p.s2[0] * h * h)) for h in (3.0, 4.0))
+    data = np.array([[1.5, -0.75, 0.5]], np.float32)[:, :n_t]
+    p = dataclasses.replace(p, src=src, rec=rec, bin=np.zeros(1, np.int32), t_first=T - 0.3 * p.dt, data=data)
+    if kind == "aa":
+        p = dataclasses.replace(p, aa=(12.0, 0.0, 16))
+    elif kind == "table":
+        p = survey.with_curved_ray_table(dataclasses.replace(p, weight=survey.WEIGHT_UNIT), 10.0,
+                                         amplitude=weight == survey.WEIGHT_COSCOS)
+    dp = ops.to_device(p, dtype=dtype, prec="extended" if kind == "extended" else "fp32")
+    m = np.full(p.image_shape, 2.0, np.float32)
+    if dtype != "f32":
+        p = dataclasses.replace(p, data=survey.quantise(p.data, dtype)[2])
+    ref, ref_d = oracle_lib.migrate(p), oracle_lib.demigrate(p, m)
+    assert np.any(ref) and np.any(ref_d)
+    for tile in [-1] + list(range(ops.tile_count(0))):
+        assert rel_l2(ops.migrate(dp, tile=tile).cpu().numpy(), ref) <= 1e-5, tile
+    for tile in [-1] + list(range(ops.tile_count(1))):
+        d = ops.demigrate(dp, torch.from_numpy(m).cuda(), tile=tile).cpu().numpy()
+        assert rel_l2(d, ref_d) <= 1e-5, tile
