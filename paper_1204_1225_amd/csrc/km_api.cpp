@@ -617,7 +617,7 @@ km_status zero_floats(float* p, int64_t n, hipStream_t s) {
     if (n <= 0) return KM_OK;
     const km_status st = injected("zero fill");
     if (st != KM_OK) return st;
-    const hipError_t e = km::launch_axpby(0.0f, p, 0.0f, p, n, s);
+    const hipError_t e = km::launch_zero(p, n, s);
     return e == hipSuccess ? KM_OK : hip_fail(e, "zero fill");
 }
 

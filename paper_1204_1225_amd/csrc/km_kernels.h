@@ -87,6 +87,7 @@ hipError_t launch_fir(const float* in, int64_t in_stride, float* out, int64_t ou
 // counting, reductions, probes (km_misc.hip)
 hipError_t launch_count(const Params& P, unsigned long long* counts, hipStream_t s);
 hipError_t launch_dot_f64(const float* a, const float* b, int64_t n, double* out, hipStream_t s);
+hipError_t launch_zero(float* p, int64_t n, hipStream_t s);
 hipError_t launch_axpby(float alpha, const float* x, float beta, float* y, int64_t n, hipStream_t s);
 hipError_t launch_item_costs(const Params& P, int cols_per_tile, unsigned long long* costs,
                              hipStream_t s);

@@ -207,6 +207,17 @@ __global__ __launch_bounds__(kStreamThreads) void axpby_kernel(float alpha, cons
     for (int64_t i = 4 * n4 + t; i < n; i += stride) y[i] = axpby1(alpha, x[i], beta, beta == 0.0f ? 0.0f : y[i]);
 }
 
+// Zeros, whatever the memory holds (0 x would keep a NaN).
+__global__ __launch_bounds__(kStreamThreads) void zero_f32_kernel(float* p, int64_t n) {
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kStreamThreads;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kStreamThreads + threadIdx.x; i < n; i += stride) p[i] = 0.0f;
+}
+
+hipError_t launch_zero(float* p, int64_t n, hipStream_t s) {
+    if (n > 0) hipLaunchKernelGGL(zero_f32_kernel, stream_grid(n, 4, 8192), dim3(kStreamThreads), 0, s, p, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_axpby(float alpha, const float* x, float beta, float* y, int64_t n, hipStream_t s) {
     if (n > 0) {
         if (aligned16(x) && aligned16(y))

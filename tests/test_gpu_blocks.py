@@ -401,3 +401,14 @@ def test_a_single_pair(ops, oracle_lib, n_t, kind, weight, dtype):
     for tile in [-1] + list(range(ops.tile_count(1))):
         d = ops.demigrate(dp, torch.from_numpy(m).cuda(), tile=tile).cpu().numpy()
         assert rel_l2(d, ref_d) <= 1e-5, tile
+
+
+# Nothing to add leaves zeros, whatever the output memory held.
+def test_empty_problems_overwrite_nan(ops):
+    p = survey.make_random(2, 6, 50, 5, 3, 7, 2)
+    empty = ops.to_device(p.subset(np.zeros(0, np.int64)))
+    img = torch.full(empty.image_shape, float("nan"), device="cuda")
+    assert not torch.any(ops.migrate(empty, data=torch.zeros((0, 50), device="cuda"), dtype="f32", image=img))
+    dp = ops.to_device(dataclasses.replace(p, x=p.x[:0]))
+    out = torch.full((6, 50), float("inf"), device="cuda")
+    assert not torch.any(ops.demigrate(dp, torch.zeros(dp.image_shape, device="cuda"), out=out))
