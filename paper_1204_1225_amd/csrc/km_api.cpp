@@ -489,7 +489,10 @@ int default_migrate_tile(int kind, int prec, int nz, Workgroups workgroups) {
 // / 5.4 (15 876), 122 / 122 (18 496), 220 / 205 (24 336).  Traces in random order span
 // more columns, which 12 of them share: 29.2 / 25.9 ms (table, 19 600), 165 / 144 ms
 // (lateral, 16 900); the lines are therefore drawn below the points of equal time of
-// shot order.
+// shot order, and from 3072 traces and 160 depths tables take 2 quads (16 waves x 8
+// slots): 1 / 2 / 3 quads 3.75 / 4.30 / 4.66 ms (6400), 19.9 / 20.3 / 21.0 (16 384) in shot
+// order, 5.74 / 5.24 / 5.53 and 31.5 / 29.2 / 28.5 in random order; with fewer depths half
+// of their 128-depth chunks is empty (129 depths, 15 879 traces 0.244 / 0.369 / 0.281).
 // Few traces with float32 square-root times fill the chip better with 8 slots (0.262
 // against 0.307 ms with 2040 traces, 0.245 against 0.269 ms with 2500; 0.109 against
 // 0.114 ms with 4452; 1.13 against 1.12 ms with 5184).
@@ -506,7 +509,7 @@ int default_demigrate_tile(int kind, int prec, int nz, int64_t n_traces, int64_t
     const bool alone = 2 * quad_bytes > kMaxLds;
     if (n_traces <= 4 * 256) return 5;
     if (kind == KIND_LTABLE) return n_traces >= (fp32 ? 24576 : 18432) ? 4 : !fp32 ? 5 : alone ? 2 : 3;
-    if (kind == KIND_TABLE) return n_traces >= 18432 || (n_traces >= 3072 && nz >= 160) ? 1 : alone ? 2 : 3;
+    if (kind == KIND_TABLE) return n_traces >= 18432 ? 1 : alone || (n_traces >= 3072 && nz >= 160) ? 2 : 3;
     if (kind == KIND_DSR && fp32) {
         const bool two = 3 * quad_bytes > kMaxLds;
         return alone ? 2 : n_traces < 4608 || (two && nz > 96) ? 0 : 3;
