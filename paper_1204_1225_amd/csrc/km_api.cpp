@@ -454,6 +454,9 @@ int64_t migrate_workgroups(int shape, const km_grid& g) {
 //                      0.76 / 0.78    1274 0.87 / 1.23 / 1.32
 //   lateral tables     480 9.26 / 8.60 / 6.90    696 7.01 / 5.84 / 8.40    1224 54.9 /
 //                      47.0 / 53.0    2352 40.8 / 45.6 / 50.4
+// A batch's workgroups take their items from a queue, so larger tiles fill the chip
+// sooner: float32 528 0.612 / 0.393 / 0.416, 656 0.350 / 0.372 / 0.411, 1072 0.425 /
+// 0.468 / 0.599; extended 1328 1.64 / 1.61 / 1.99, 1664 1.78 / 1.88 / 2.50.
 // Below, 256 workgroups of tile 7 ran 0.29 ms against 0.38 ms with tile 8, 128 of them
 // 0.090 against 0.065 ms (square-root times).
 // Tile 2 (128 columns) with invariant tables from 8192 workgroups, where staging whole
@@ -462,11 +465,13 @@ int64_t migrate_workgroups(int shape, const km_grid& g) {
 // grid of tile 5 would pass 2^31 threads.  Depths that need more than kMaxChunks
 // chunks of 128 take chunks of 256 with laterally varying tables.
 template <typename Workgroups>
-int default_migrate_tile(int kind, int prec, int nz, Workgroups workgroups) {
+int default_migrate_tile(int kind, int prec, int nz, bool batch, Workgroups workgroups) {
     if (kind == KIND_LTABLE && nz > 128 * kMaxChunks) return 3;
     const int64_t wide = workgroups(5);  // 64 columns x 128 depths
     if (wide >= int64_t{1} << 22 || (kind == KIND_TABLE && wide >= 8192)) return 2;
-    const int64_t line = kind == KIND_DSR      ? (prec == KM_TIME_EXTENDED ? 3600 : 1800)
+    const bool ext = prec == KM_TIME_EXTENDED;
+    const int64_t line = batch                 ? (ext ? 1600 : 640)
+                         : kind == KIND_DSR    ? (ext ? 3600 : 1800)
                          : kind == KIND_LTABLE ? 2400
                          : kind == KIND_TABLE  ? 800
                                                : 640;
@@ -636,7 +641,7 @@ km_status migrate_impl(const km_traces* traces, const km_grid* grid, const km_tr
     int shape = 0;
     const int kind = lat ? KIND_LTABLE : tab ? KIND_TABLE : aa ? KIND_AA : KIND_DSR;
     st = pick_tile(0, tile, traces->dtype, kind, tt->time_precision, grid->nz, traces->n_samples, image_columns(*grid),
-                   [&] { return default_migrate_tile(kind, tt->time_precision, grid->nz, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
+                   [&] { return default_migrate_tile(kind, tt->time_precision, grid->nz, false, [&](int sh) { return migrate_workgroups(sh, *grid); }); },
                    &shape);
     if (st != KM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1144,7 +1149,7 @@ km_status batch_plan(const km_problem* probs, int32_t n, int32_t tile, int64_t m
     };
     const auto fits = [&](int t) { return workgroups(t % kTileLevelStride) <= max_items; };
     const auto untuned = [&] {
-        const int t = default_migrate_tile(KIND_DSR, probs[0].tt.time_precision, max_nz, workgroups);
+        const int t = default_migrate_tile(KIND_DSR, probs[0].tt.time_precision, max_nz, true, workgroups);
         return fits(t) ? t : 2;
     };
     km_status st = pick_tile(0, tile, probs[0].traces.dtype, KIND_DSR, probs[0].tt.time_precision, max_nz, max_nt,
