@@ -13,18 +13,19 @@
 // derives from ballots which 16-depth slots can hold a pair inside the aperture
 // and which are wholly inside, and evaluates those slots two at a time.  The
 // source leg's share of a pair is kept from trace to trace while the source
-// stays the same (SrcLeg), unless the traces seldom share it (own_legs); the receiver's
-// costs one square root, the weight one reciprocal, then the sample index and fraction, one 8-byte LDS read of the
-// staged (sample, difference) pair, the interpolation and, at the aperture's
-// edge, the lane's mask.  Table times and the anti-alias filter use the same
+// stays the same (SrcLeg), unless the traces seldom share it (own_legs); the
+// receiver's costs one square root, the weight one reciprocal, then the sample
+// index and fraction, one 8-byte LDS read of the staged (sample, difference)
+// pair, the interpolation and, at the aperture's edge, the lane's mask.  Table times and the anti-alias filter use the same
 // blocks with their own staged forms (plain samples; float64 double running
 // sums, one slot at a time).  With 16-bit traces the S16 kernels keep the
 // samples' 16-bit storage in LDS instead (packed pairs; single samples for table
 // times) and widen them on read.
 //
-// What bounds it: VALU issue (93 % of it on a survey of 200 000 traces over 16 x
-// 128 x 128 x 400 points, 5.2e11 pairs; transcendentals take 2.4 issue slots
-// each).  394 -> 316 ms there from keeping source legs, testing the aperture
+// What bounds it: VALU issue (200 000 traces over 16 x 256 x 256 x 400 points:
+// 19.4 lane-slots per pair inside the aperture, 2.6 of them transcendentals of 2.3
+// issue slots each, together 89 % of the slots; waits for LDS 0.5 % of the
+// wavefronts' cycles).  394 -> 318 ms over 16 x 128 x 128 x 400 points from keeping source legs, testing the aperture
 // only at its edge (13 instead of 15 VALU instructions per pair and lane),
 // reading a trace's row and clamp bounds by one broadcast, and staging 4
 // samples per lane; evaluating single slots where only one of a pair is inside
@@ -407,8 +408,9 @@ __device__ __forceinline__ void mig_slot_aa(float A, float B, float ss, float is
 
 // The source legs of every slot from the leg's squared length (float32 and,
 // for the extended kernels, float64).  vd, vl: byte offset of the lane's depth in
-// slot 0 of a table row, and how far it is to the table's last depth.  Table slot pairs that no lane of the wavefront can use
-// are not read (a pair is evaluated whole, so both its slots are filled).
+// slot 0 of a table row, and how far it is to the row's last depth.  Table slot pairs
+// that no lane of the wavefront can use are not read (a pair is evaluated whole, so
+// both its slots are filled).
 template <int KS, int WK, int TT, bool PX>
 __device__ __forceinline__ void source_leg(const Params& P, const ChunkTables<KS>& T, float hs2, double Hs, LCol C,
                                            int vd, int vl, SrcLeg<KS, TT, PX>& S) {
@@ -586,7 +588,10 @@ __device__ __forceinline__ void migrate_tile(const Params& P, int64_t lo, int64_
     load_chunk_tables<KS, 1, TT, PX>(P, z0, z1, d, WK == W_COSCOS, T, sR);
 
     constexpr bool LAT = TT == TT_LTABLE;
-    // bytes from the lane's depth in slot 0 to the table's last: a lane past it reads that one
+    // bytes from the lane's depth in slot 0 to the row's last: a lane past it reads that one.
+    // The clamp costs two operations per read (2.64 s for 200 000 traces -> 16 x 256 x 256 x
+    // 400 points, 2.54 s without); a second body for the chunks that need none ran 2.59 s
+    // there, but 5.34 against 5.12 ms on 25 600 traces -> 8 x 80 x 80 x 152.
     const int vl = 4 * (P.nz - 1 - z0 - d);
     // first column of the wavefront's groups; group q's lane column is col0 + 4 q + g
     const int col0 = (tile * NC + cw) * CWQ * kGroupsPerWave;
@@ -1311,7 +1316,7 @@ static hipError_t launch_migrate_batch_shape(const Params* probs, const int4* it
 
 // Waves, column groups per wave, depth slots, LDS budget for the trace block,
 // trace parts.  The small tiles (ms, square-root times, before: 8 waves x 4 groups):
-//   1536 traces -> 8 x 128 x 200 points    0.521 -> 0.065  (16 waves, 4 parts, 4 slots)
+//   1536 traces -> 8 x 128 x 200 points    0.521 -> 0.058  (16 waves, 4 parts, 4 slots)
 //   6144 traces -> 8 x 256 x 256           1.91  -> 0.289  (16 waves, 4 parts, 8 slots)
 //   16384 traces -> 16 x 512 x 400         2.57  -> 1.89   (4 waves, 1 group)
 //   20736 traces -> 10 x 80 x 80 x 300     17.9  -> 14.6   (8 waves, 2 groups)
